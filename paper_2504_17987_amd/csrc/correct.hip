@@ -3,9 +3,12 @@
 // over the search shifts (Pearson coefficient), pick the best shift and fit
 // a 3-point Gaussian per axis.
 //
-// Two implementations of the same definition:
+// Implementations of the same definition:
 //  * k_correct_generic -- one workgroup per window; any window/step/radius.
-//  * k_correct_tiled   -- the fast path for 50%-overlap windows (win = 2 step):
+//  * k_correct_rows    -- 32 px windows at 50% overlap (below).
+//  * k_correct_bands   -- 16 and 24 px windows at 50% overlap, frame B
+//    deformed (below).
+//  * k_correct_tiled   -- the other cases of 50%-overlap windows (win = 2 step):
 //    a workgroup owns a TW x TH tile of windows; the deformed B' tile and the
 //    A tile live in LDS; each thread correlates one step x step cell with a
 //    band of SYG shift rows, so every pixel-shift product is formed once and
@@ -17,6 +20,8 @@
 // unchanged and keeps E[x^2] - E[x]^2 well conditioned.  A window counts as
 // flat when its variance is below 1e-6 of its second moment about K (an
 // exact zero cannot be certified in FP32); a flat window has coefficient 0.
+#include <type_traits>
+
 #include "dev_common.h"
 #include "piv_internal.h"
 
@@ -1643,6 +1648,502 @@ void k_correct_bands(CorrArgs g) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Thread per (cell, shift row): 50%-overlap windows of large cells (win = 32,
+// step 16).  A cell times its shifts is more work than a lane should hold
+// and a tile of 63 cells more than a small frame has, so here a thread takes
+// one cell, one row of shifts and one of PARTS interleaved parts of the
+// cell's rows: it streams those rows of A and B' from LDS and keeps 2R+1
+// sums of products.  PARTS neighbouring lanes add up by DPP, the cells' sums
+// meet in LDS, and a thread per (window, shift row) forms the coefficients.
+// The box sums S and Q of B' are taken per window, columns first (a thread
+// per column and window row), then along the row: sums over the rows
+// (columns) that every shift shares, plus running sums at both ends, so that
+// nothing is subtracted.  Frames are deformed by the whole predictor (B
+// only), or by half of it each (kCentral; A' is then held as floats, else
+// the packed pixels are).
+// ---------------------------------------------------------------------------
+template <typename T, int STEP, int R, int TW, int TH, int PARTS, int NT, bool kCentral>
+struct RowsCfg {
+  static constexpr int ES = (int)sizeof(T);
+  static constexpr int CW = TW + 1, CH = TH + 1, NC = CW * CH, NWIN = TW * TH;
+  static constexpr int NSY = 2 * R + 1, WIN = 2 * STEP;
+  static constexpr int AW = CW * STEP, AH = CH * STEP;
+  static constexpr int BW = AW + 2 * R, BH = AH + 2 * R;
+  static constexpr int odd4(int n) { return 4 * (((n + 3) / 4) | 1); }   // whole odd groups of four: rows spread over the banks
+  static constexpr int BP = odd4(BW);
+  static constexpr int AP = kCentral ? odd4(AW) : AW * ES / 4;           // words
+  static constexpr int NNX = BW / STEP + 4, NNY = BH / STEP + 3;         // predictor nodes of the B' tile
+  static constexpr int BRW = STEP + 2 * R;                               // B' columns of one cell
+  static constexpr int WRW = WIN + 2 * R;                                // B' columns of one window
+  static constexpr int PP = (NSY + 3) / 4 * 4;                           // sums of one item, padded
+  static constexpr int NI = NC * NSY * PARTS;                            // items (threads) of the products
+  // raw source box: the tile plus a predictor range of 17 px across it
+  static constexpr int RAW = (BH + 20) * (((BW + 20) * ES + 3) / 4 + 2);
+  static constexpr int VS = TH * NSY * BP, PW = NC * NSY * PP;
+  // [raw box, then the column sums S and Q] [A] [B', then the cells' sums]
+  static constexpr int AWORDS = AH * AP;
+  static constexpr int RV = kCentral ? (2 * VS > RAW + AWORDS ? 2 * VS - AWORDS : RAW) : (2 * VS > RAW ? 2 * VS : RAW);
+  static constexpr int BWORDS = BH * BP > PW ? BH * BP : PW;
+  static constexpr int TOTAL = (RV + 3) / 4 * 4 + AWORDS + BWORDS;
+  static_assert(NI <= NT, "one item per thread");
+  static_assert(NWIN * NSY <= NT, "a thread per window and shift row");
+  static_assert(STEP == 16 && STEP % PARTS == 0 && (PARTS & (PARTS - 1)) == 0 && PARTS <= 16, "parts add up by DPP");
+};
+
+template <typename T, int STEP, int R, int TW, int TH, int PARTS, int NT, bool kCentral>
+__global__ __launch_bounds__(NT) void k_correct_rows(CorrArgs g) {
+  using C = RowsCfg<T, STEP, R, TW, TH, PARTS, NT, kCentral>;
+  constexpr int ES = C::ES, NSY = C::NSY;
+  __shared__ __align__(16) float s_mem[C::TOTAL];
+  __shared__ float s_rho[C::NWIN * NSY * NSY];
+  __shared__ float s_best[C::NWIN * NSY];
+  __shared__ int s_key[C::NWIN * NSY];   // tie key << 1 | every used shift of the row flat
+  __shared__ float s_node[2][C::NNY][C::NNX];
+  __shared__ int s_rb[C::BH], s_cb[(C::BW + 3) / 4 * 4];
+  __shared__ float s_rf[C::BH], s_cf[(C::BW + 3) / 4 * 4];
+  __shared__ float s_ca[2][C::NC];       // per cell: sum of A - K and of its square
+  __shared__ float s_red[(NT + 63) / 64];
+  float* const sV = s_mem;
+  uint32_t* const sraw = reinterpret_cast<uint32_t*>(s_mem);
+  float* const sA = s_mem + (C::RV + 3) / 4 * 4;
+  uint32_t* const sAw = reinterpret_cast<uint32_t*>(sA);
+  float* const sB = sA + C::AWORDS;
+
+  const WgIdx wg = xcd_order();
+  const int pair = wg.z;
+  if (slot_off(g.mask, pair)) return;
+  const int t = threadIdx.x, lane = t & 63;
+  const int a0 = wg.y * TH, b0 = wg.x * TW;
+  const int y0 = a0 * STEP - STEP / 2, x0 = b0 * STEP - STEP / 2;   // A tile origin
+  const int yb = y0 - R, xb = x0 - R;                              // B' tile origin
+  const uint8_t* Ai = g.A + (int64_t)pair * g.stride;
+  const uint8_t* Bi = g.B + (int64_t)pair * g.stride;
+  const int np = g.nx * g.ny, rowbytes = g.W * ES;
+  const float* Pn = g.pred ? g.pred + (int64_t)pair * 2 * np : nullptr;
+
+  // predictor nodes covering the B' tile: every wave reads all of them and
+  // takes their range itself
+  const float cen = 0.5f * (float)(STEP - 1);
+  const int nlo_y = max(0, (int)floorf(((float)yb - cen) / STEP));
+  const int nlo_x = max(0, (int)floorf(((float)xb - cen) / STEP));
+  constexpr int NNODE = C::NNY * C::NNX, NL = (NNODE + 63) / 64;
+  float nu[NL], nv[NL];
+  if (Pn) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int idx = min(lane + 64 * i, NNODE - 1);
+      const int r = idx / C::NNX, q = idx - (idx / C::NNX) * C::NNX;
+      const int o = min(nlo_y + r, g.ny - 1) * g.nx + min(nlo_x + q, g.nx - 1);
+      nu[i] = Pn[o];
+      nv[i] = Pn[np + o];
+    }
+  }
+  // the A tile as packed pixels (zero outside the image), and its sum
+  float asum = 0.0f;
+  if constexpr (!kCentral) {
+    int isum = 0;
+    constexpr int NA = (C::AWORDS + NT - 1) / NT;
+    uint32_t w[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const int idx = min(t + i * NT, C::AWORDS - 1);
+      const int r = idx / C::AP, k = idx - (idx / C::AP) * C::AP;
+      const int y = y0 + r;
+      const uint32_t ok = (t + i * NT < C::AWORDS && (unsigned)y < (unsigned)g.H) ? 0xffffffffu : 0u;
+      w[i] = masked_word(Ai + (int64_t)min(max(y, 0), g.H - 1) * g.pitch, rowbytes, x0 * ES + 4 * k) & ok;
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      if (t + i * NT < C::AWORDS) sAw[t + i * NT] = w[i];
+      isum = ES == 1 ? (int)__builtin_amdgcn_sad_u8(w[i], 0u, (uint32_t)isum)
+                     : (int)__builtin_amdgcn_sad_u16(w[i], 0u, (uint32_t)isum);
+    }
+    asum = (float)wave_sum(isum);
+  }
+  // interpolation tables of the B' tile (the same arithmetic as interp_u;
+  // columns past BW pad the last group: written to B', never correlated)
+  constexpr int BW4 = (C::BW + 3) / 4 * 4;
+  for (int i = t; i < C::BH + BW4; i += NT) {
+    const bool row = i < C::BH;
+    const int p = row ? yb + i : xb + (i - C::BH);
+    const int n = row ? g.ny : g.nx;
+    const float tt = fminf(fmaxf(((float)p - cen) / (float)STEP, 0.0f), (float)(n - 1));
+    const int bb = min((int)tt, max(n - 2, 0));
+    const float ff = tt - (float)bb;
+    if (row) { s_rb[i] = bb - nlo_y; s_rf[i] = ff; }
+    else { s_cb[i - C::BH] = bb - nlo_x; s_cf[i - C::BH] = ff; }
+  }
+  // range of the nodes; a node that is not finite or not below 100 px marks
+  // the tile, which sends it to the checked path
+  float lu = 0.0f, hu = 0.0f, lv = 0.0f, hv = 0.0f;
+  bool sane = true;
+  if (Pn) {
+    lu = hu = nu[0];
+    lv = hv = nv[0];
+    bool ok = true;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      lu = fminf(lu, nu[i]);
+      hu = fmaxf(hu, nu[i]);
+      lv = fminf(lv, nv[i]);
+      hv = fmaxf(hv, nv[i]);
+      ok = ok && fabsf(nu[i]) < 100.0f && fabsf(nv[i]) < 100.0f;   // false for NaN
+    }
+    lu = wave_min(lu);
+    hu = wave_max(hu);
+    lv = wave_min(lv);
+    hv = wave_max(hv);
+    sane = __all(ok) && hu - lu < 64.0f && hv - lv < 64.0f;
+    if (t < 64) {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        const int idx = lane + 64 * i;
+        if (idx < NNODE) {
+          const int r = idx / C::NNX, q = idx - (idx / C::NNX) * C::NNX;
+          s_node[0][r][q] = nu[i];
+          s_node[1][r][q] = nv[i];
+        }
+      }
+    }
+  }
+  // The raw source box of a frame for the deformation of the tile rows x
+  // cols at (ty, tx) by s * u, staged when it fits: every real sample lands
+  // at >= 1 and its right and lower neighbours in the box (a one-pixel
+  // margin around the nodes' range).
+  struct Box { int ix0, ix1, iy0, iy1, nwords; bool staged; };
+  auto stage = [&](const uint8_t* img, int ty, int tx, int rows, int cols, float s) __attribute__((always_inline)) {
+    const float xl = s < 0.0f ? s * hu : s * lu, xh = s < 0.0f ? s * lu : s * hu;
+    const float yl = s < 0.0f ? s * hv : s * lv, yh = s < 0.0f ? s * lv : s * hv;
+    Box b;
+    b.ix0 = sane ? tx + (int)floorf(xl) - 1 : 0;
+    b.ix1 = sane ? tx + cols - 1 + (int)floorf(xh) + 2 : 0;
+    b.iy0 = sane ? ty + (int)floorf(yl) - 1 : 0;
+    b.iy1 = sane ? ty + rows - 1 + (int)floorf(yh) + 2 : 0;
+    const int xw0 = (b.ix0 * ES) >> 2;
+    b.nwords = ((b.ix1 * ES + ES - 1) >> 2) - xw0 + 1;
+    const int nrows = b.iy1 - b.iy0 + 1;
+    b.staged = sane && b.nwords <= NT && b.nwords * nrows <= C::RAW;
+    if (b.staged) {
+      const int rstep = NT / b.nwords, r0 = t / b.nwords, w = t - r0 * b.nwords;
+      constexpr int U = 8;   // reads in flight per thread
+      if (r0 < rstep) {
+        for (int rb = r0; rb < nrows; rb += U * rstep) {
+          uint32_t val[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            // (slots past the box take its last row again: the same word is
+            // written twice with the same value)
+            const int y = b.iy0 + min(rb + u * rstep, nrows - 1);
+            const uint32_t ok = (unsigned)y < (unsigned)g.H ? 0xffffffffu : 0u;
+            val[u] = masked_word(img + (int64_t)min(max(y, 0), g.H - 1) * g.pitch, rowbytes, 4 * (xw0 + w)) & ok;
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) sraw[min(rb + u * rstep, nrows - 1) * b.nwords + w] = val[u];
+        }
+      }
+    }
+    return b;
+  };
+  // deformed tile rows x cols4 (whole groups of four columns) at (ty, tx),
+  // table rows / columns from (tr, tc), minus K, into dst
+  auto deform = [&](const uint8_t* img, const Box& b, int ty, int tx, int rows, int cols4, int tr, int tc, float s,
+                    float K, float* dst, int pitch, float& sum, auto uniform) __attribute__((always_inline)) {
+    // uniform: no group of four straddles a node column
+    constexpr bool kUni = decltype(uniform)::value;
+    const int nq = cols4 / 4;
+    const uint8_t* rawb = reinterpret_cast<const uint8_t*>(sraw);
+    const int rowb = 4 * b.nwords, xadd = b.ix0 * ES - 4 * ((b.ix0 * ES) >> 2);
+    const unsigned ixhi = (unsigned)(b.ix1 - 1 - b.ix0), iyhi = (unsigned)(b.iy1 - 1 - b.iy0);
+    for (int idx = t; idx < rows * nq; idx += NT) {
+      const int r = idx / nq, q = 4 * (idx - (idx / nq) * nq);
+      float out[4];
+      if (b.staged) {
+        float Vu[3] = {0.0f, 0.0f, 0.0f}, Vv[3] = {0.0f, 0.0f, 0.0f};
+        int cb0 = 0;
+        if (Pn) {
+          const int rb = s_rb[tr + r];
+          const float fy = s_rf[tr + r];
+          cb0 = s_cb[tc + q];
+          // (a group of four pixels spans at most two cells: three node columns)
+#pragma unroll
+          for (int j = 0; j < (kUni ? 2 : 3); ++j) {
+            const float u0 = s_node[0][rb][cb0 + j], v0 = s_node[1][rb][cb0 + j];
+            Vu[j] = u0 + fy * (s_node[0][rb + 1][cb0 + j] - u0);
+            Vv[j] = v0 + fy * (s_node[1][rb + 1][cb0 + j] - v0);
+          }
+        }
+        const float yr = (float)(ty + r - b.iy0), xq = (float)(tx + q - b.ix0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float u = 0.0f, v = 0.0f;
+          if (Pn) {
+            const bool nxt = !kUni && s_cb[tc + q + e] != cb0;
+            const float fx = s_cf[tc + q + e];
+            const float ul = nxt ? Vu[1] : Vu[0], ur = nxt ? Vu[2] : Vu[1];
+            const float vl = nxt ? Vv[1] : Vv[0], vr = nxt ? Vv[2] : Vv[1];
+            u = s * (ul + fx * (ur - ul));
+            v = s * (vl + fx * (vr - vl));
+          }
+          const float qx = (xq + (float)e) + u, qy = yr + v;
+          const float fx = __builtin_amdgcn_fractf(qx), fy = __builtin_amdgcn_fractf(qy);
+          // (the clamps only keep padding columns inside the box)
+          const unsigned ix = min((unsigned)(int)qx, ixhi), iy = min((unsigned)(int)qy, iyhi);
+          const uint8_t* p0 = rawb + (__umul24(iy, (unsigned)rowb) + ix * ES + xadd);
+          auto px = [](const uint8_t* p) -> float { return (float)*reinterpret_cast<const T*>(p); };
+          const float p00 = px(p0), p01 = px(p0 + ES), p10 = px(p0 + rowb), p11 = px(p0 + rowb + ES);
+          const float top = p00 + fx * (p01 - p00), bot = p10 + fx * (p11 - p10);
+          out[e] = (top + fy * (bot - top)) - K;
+        }
+      } else {
+#pragma unroll 1
+        for (int e = 0; e < 4; ++e) {
+          const int y = ty + r, x = tx + q + e;
+          float v;
+          if (Pn) {
+            const int rb = s_rb[tr + r], cb = s_cb[tc + q + e];
+            const float fy = s_rf[tr + r], fx = s_cf[tc + q + e];
+            const float u = (1.0f - fy) * ((1.0f - fx) * s_node[0][rb][cb] + fx * s_node[0][rb][cb + 1]) +
+                            fy * ((1.0f - fx) * s_node[0][rb + 1][cb] + fx * s_node[0][rb + 1][cb + 1]);
+            const float w = (1.0f - fy) * ((1.0f - fx) * s_node[1][rb][cb] + fx * s_node[1][rb][cb + 1]) +
+                            fy * ((1.0f - fx) * s_node[1][rb + 1][cb] + fx * s_node[1][rb + 1][cb + 1]);
+            v = bilin<T>(img, g.pitch, g.W, g.H, (float)x + s * u, (float)y + s * w);
+          } else {
+            v = pixf<T>(img, g.pitch, g.W, g.H, y, x);
+          }
+          out[e] = v - K;
+        }
+      }
+      sum += (out[0] + out[1]) + (out[2] + out[3]);
+      *reinterpret_cast<float4*>(dst + r * pitch + q) = make_float4(out[0], out[1], out[2], out[3]);
+    }
+  };
+
+  if constexpr (kCentral) {
+    const Box ab = stage(Ai, y0, x0, C::AH, C::AW, -0.5f);
+    __syncthreads();
+    deform(Ai, ab, y0, x0, C::AH, C::AW, R, R, -0.5f, 0.0f, sA, C::AP, asum, std::true_type());
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) asum += __shfl_xor(asum, o);
+    __syncthreads();   // the raw box of A is read
+  }
+  if (lane == 0) s_red[t >> 6] = asum;
+  const Box bb = stage(Bi, yb, xb, C::BH, C::BW, kCentral ? 0.5f : 1.0f);
+  __syncthreads();
+  // the tile offset K: the rounded mean of the A tile
+  float K = 0.0f;
+#pragma unroll
+  for (int i = 0; i < (NT + 63) / 64; ++i) K += s_red[i];
+  K = rintf(K / (float)(C::AH * C::AW));
+  float unused = 0.0f;
+  deform(Bi, bb, yb, xb, C::BH, BW4, 0, 0, kCentral ? 0.5f : 1.0f, K, sB, C::BP, unused,
+         std::bool_constant<(STEP + R) % 4 == 0>());
+  __syncthreads();
+
+  // pixel x of a cell row of A
+  auto arow = [&](int cy, int cx, int py, float (&ar)[STEP]) __attribute__((always_inline)) {
+    if constexpr (kCentral) {
+      const float* p = sA + (cy * STEP + py) * C::AP + cx * STEP;
+#pragma unroll
+      for (int x = 0; x < STEP; ++x) ar[x] = p[x];
+    } else {
+      const uint32_t* p = sAw + (cy * STEP + py) * C::AP + cx * (STEP * ES / 4);
+      uint32_t w[STEP * ES / 4];
+#pragma unroll
+      for (int k = 0; k < STEP * ES / 4; ++k) w[k] = p[k];
+#pragma unroll
+      for (int x = 0; x < STEP; ++x) {
+        const uint32_t wd = w[(x * ES) >> 2];
+        ar[x] = (float)(ES == 1 ? (wd >> (8 * (x & 3))) & 0xffu : (wd >> (16 * (x & 1))) & 0xffffu);
+      }
+    }
+  };
+  // sums over the lanes of one item (or the 16 rows of a cell): neighbouring
+  // lanes by quad permutes, then the half-row and row mirrors
+  auto lanes_sum = [](float v, int n) {
+    auto dpp = [](float x, auto ctrl) {
+      return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, false));
+    };
+    if (n > 1) v += dpp(v, std::integral_constant<int, 0xB1>());
+    if (n > 2) v += dpp(v, std::integral_constant<int, 0x4E>());
+    if (n > 4) v += dpp(v, std::integral_constant<int, 0x141>());
+    if (n > 8) v += dpp(v, std::integral_constant<int, 0x140>());
+    return v;
+  };
+  // ---- products: P = sum A (B' - K) over the thread's rows of its cell
+  const int q = t / PARTS, part = t - q * PARTS;
+  const int sy_i = q % NSY, cell = q / NSY;
+  float P[NSY];
+  if (t < C::NI) {
+    const int ci = cell / C::CW, cj = cell - (cell / C::CW) * C::CW;
+#pragma unroll
+    for (int j = 0; j < NSY; ++j) P[j] = 0.0f;
+    const float* bbase = sB + (ci * STEP + sy_i) * C::BP + cj * STEP;
+    // one row at a time in flight beside the one worked on
+#pragma unroll 2
+    for (int k = 0; k < STEP / PARTS; ++k) {
+      const int py = part + PARTS * k;
+      float ar[STEP], br[C::BRW];
+      arow(ci, cj, py, ar);
+#pragma unroll
+      for (int x = 0; x < C::BRW; ++x) br[x] = bbase[py * C::BP + x];
+#pragma unroll
+      for (int x = 0; x < STEP; ++x)
+#pragma unroll
+        for (int j = 0; j < NSY; ++j) P[j] += ar[x] * br[x + j];
+    }
+#pragma unroll
+    for (int j = 0; j < NSY; ++j) P[j] = lanes_sum(P[j], PARTS);
+  }
+  // ---- per cell: sum of A - K and of its square, a lane per cell row
+  for (int i = t; i < (16 * C::NC + 63) / 64 * 64; i += NT) {
+    const int c = min(i >> 4, C::NC - 1), py = i & 15;
+    float ar[STEP], s1 = 0.0f, s2 = 0.0f;
+    arow(c / C::CW, c - (c / C::CW) * C::CW, py, ar);
+#pragma unroll
+    for (int x = 0; x < STEP; ++x) {
+      const float d = ar[x] - K;
+      s1 += d;
+      s2 += d * d;
+    }
+    s1 = lanes_sum(s1, 16);
+    s2 = lanes_sum(s2, 16);
+    if (py == 0) {
+      s_ca[0][c] = s1;
+      s_ca[1][c] = s2;
+    }
+  }
+  if constexpr (kCentral) __syncthreads();   // A' is read: the column sums take its place
+  // ---- column sums of B' over every window row and row shift
+  for (int i = t; i < TH * C::BW; i += NT) {
+    const int wi = i / C::BW, x = i - (i / C::BW) * C::BW;
+    const float* col = sB + wi * STEP * C::BP + x;
+    float* vs = sV + wi * NSY * C::BP + x;
+    float* vq = vs + C::VS;
+    float head[2 * R], s = 0.0f, q2 = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 2 * R; ++r) head[r] = col[r * C::BP];
+#pragma unroll 8
+    for (int r = 2 * R; r < C::WIN; ++r) {
+      const float v = col[r * C::BP];
+      s += v;
+      q2 += v * v;
+    }
+    // rows the shift takes from the head, last row first, then the tail's
+    float hs[NSY], hq[NSY];
+    hs[2 * R] = hq[2 * R] = 0.0f;
+#pragma unroll
+    for (int r = 2 * R - 1; r >= 0; --r) {
+      hs[r] = hs[r + 1] + head[r];
+      hq[r] = hq[r + 1] + head[r] * head[r];
+    }
+    float ts = 0.0f, tq = 0.0f;
+#pragma unroll
+    for (int k = 0; k < NSY; ++k) {
+      if (k > 0) {
+        const float v = col[(C::WIN + k - 1) * C::BP];
+        ts += v;
+        tq += v * v;
+      }
+      vs[k * C::BP] = hs[k] + s + ts;
+      vq[k * C::BP] = hq[k] + q2 + tq;
+    }
+  }
+  __syncthreads();   // B' is read: the cells' sums take its place
+  if (t < C::NI && part == 0) {
+    float* o = sB + (sy_i * C::NC + cell) * C::PP;
+#pragma unroll
+    for (int j = 0; j < NSY; ++j) o[j] = P[j];
+  }
+  __syncthreads();
+  // ---- a thread per (window, shift row): coefficients and the row's peak
+  if (t < C::NWIN * NSY) {
+    const int w = t / NSY, k = t - w * NSY, sy = k - R;
+    const int wi = w / TW, wj = w - (w / TW) * TW;
+    constexpr float kInvN = 1.0f / (float)(C::WIN * C::WIN);
+    const int c00 = wi * C::CW + wj, c10 = c00 + C::CW;
+    const float sa = (s_ca[0][c00] + s_ca[0][c00 + 1]) + (s_ca[0][c10] + s_ca[0][c10 + 1]);
+    const float saa = (s_ca[1][c00] + s_ca[1][c00 + 1]) + (s_ca[1][c10] + s_ca[1][c10 + 1]);
+    const float mA = sa * kInvN, varA = saa - sa * mA, meanA = K + mA;
+    const bool flatA = !(varA > kFlatRel * saa);
+    // box sums along the row of column sums
+    float S[NSY], Q[NSY];
+    auto boxes = [&](const float* p, float (&o)[NSY]) __attribute__((always_inline)) {
+      float head[NSY], mid = 0.0f, tail = 0.0f;
+      head[2 * R] = 0.0f;
+#pragma unroll
+      for (int x = 2 * R - 1; x >= 0; --x) head[x] = head[x + 1] + p[x];
+#pragma unroll
+      for (int x = 2 * R; x < C::WIN; ++x) mid += p[x];
+#pragma unroll
+      for (int j = 0; j < NSY; ++j) {
+        if (j > 0) tail += p[C::WIN + j - 1];
+        o[j] = head[j] + mid + tail;
+      }
+    };
+    const float* vs = sV + (wi * NSY + k) * C::BP + wj * STEP;
+    boxes(vs, S);
+    boxes(vs + C::VS, Q);
+    const float* p00 = sB + (k * C::NC + c00) * C::PP;
+    const float* p10 = p00 + C::CW * C::PP;
+    float best = -2.0f;
+    int bkey = 1 << 20;
+    bool allflat = true;
+#pragma unroll
+    for (int j = 0; j < NSY; ++j) {
+      const int sx = j - R;
+      const float Pw = (p00[j] + p00[C::PP + j]) + (p10[j] + p10[C::PP + j]);
+      const float num = Pw - meanA * S[j];
+      const float varB = Q[j] - S[j] * S[j] * kInvN;
+      const bool flat = flatA || !(varB > kFlatRel * Q[j]);
+      const float r = flat ? 0.0f : num * __builtin_amdgcn_rsqf(varA * varB);
+      s_rho[t * NSY + j] = r;
+      const bool used = !g.fixed || sx == 0 || sy == 0;
+      if (used) {
+        allflat = allflat && flat;
+        const int key = tie_key(sy, sx);
+        if (better(r, key, best, bkey)) {
+          best = r;
+          bkey = key;
+        }
+      }
+    }
+    s_best[t] = best;
+    s_key[t] = (bkey << 1) | (allflat ? 1 : 0);
+  }
+  __syncthreads();
+  // ---- a thread per window: its peak, fit, composition
+  if (t < C::NWIN) {
+    const int wi = t / TW, a = a0 + wi, b = b0 + t - wi * TW;
+    if (a < g.ny && b < g.nx) {
+      float best = -2.0f;
+      int bkey = 1 << 20;
+      bool allflat = true;
+#pragma unroll
+      for (int k = 0; k < NSY; ++k) {
+        const int kk = s_key[t * NSY + k];
+        const float r = s_best[t * NSY + k];
+        allflat = allflat && (kk & 1);
+        if (better(r, kk >> 1, best, bkey)) {
+          best = r;
+          bkey = kk >> 1;
+        }
+      }
+      int sy = 0, sx = 0;
+      if (!g.fixed) {
+        sx = (bkey & 63) - 32;
+        sy = ((bkey >> 6) & 63) - 32;
+      }
+      const float* rr = s_rho + t * NSY * NSY;
+      auto rhof = [&](int y, int x) { return rr[(y + R) * NSY + x + R]; };
+      auto node = [&](int c, int y, int x) { return s_node[c][y - nlo_y][x - nlo_x]; };
+      float pu = 0.0f, pv = 0.0f;
+      if (Pn) window_mean_half_overlap(a, b, g.nx, g.ny, node, pu, pv);
+      finish_vector(g, pair, a, b, sy, sx, allflat, pu, pv, rhof);
+    }
+  }
+}
+
 template <typename T, int STEP, int R, int SYG, int TW, int TH, int NT>
 hipError_t launch_tiled(const CorrArgs& g, int n, hipStream_t s) {
   dim3 grid((g.nx + TW - 1) / TW, (g.ny + TH - 1) / TH, n);
@@ -1657,6 +2158,17 @@ hipError_t launch_bands(const CorrArgs& g, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <typename T, int STEP, int R, int TW, int TH, int PARTS, int NT>
+hipError_t launch_rows(const CorrArgs& g, int n, hipStream_t s) {
+  dim3 grid((g.nx + TW - 1) / TW, (g.ny + TH - 1) / TH, n);
+  // (without a predictor the symmetric deformation moves nothing)
+  if (g.central && g.pred)
+    hipLaunchKernelGGL((k_correct_rows<T, STEP, R, TW, TH, PARTS, NT, true>), grid, dim3(NT), 0, s, g);
+  else
+    hipLaunchKernelGGL((k_correct_rows<T, STEP, R, TW, TH, PARTS, NT, false>), grid, dim3(NT), 0, s, g);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_tiled_t(const CorrArgs& g, int n, hipStream_t s) {
   if (!g.central && g.step == 8 && g.R == 4) return launch_bands<T, 8, 4, 3, 8, 6>(g, n, s);
@@ -1668,6 +2180,20 @@ hipError_t launch_tiled_t(const CorrArgs& g, int n, hipStream_t s) {
   if (g.step == 8 && g.R == 1) return launch_tiled<T, 8, 1, 1, 8, 8, 256>(g, n, s);
   if (g.step == 12 && g.R == 4) return launch_tiled<T, 12, 4, 3, 5, 5, 128>(g, n, s);
   if (g.step == 12 && g.R == 1) return launch_tiled<T, 12, 1, 1, 5, 5, 128>(g, n, s);
+  if (g.step == 16) {
+    // Small frames take a workgroup per window with its cells' rows in many
+    // parts (latency), larger ones share cells in a tile.  For one u8 pair
+    // both take as long at about 1,100 windows for r 4 (18 and 20 us at
+    // 1,024; 26 and 20 at 1,600) and 400 for r 8 (15 and 21 us at 256; 28
+    // and 22 at 576), but a batch gains from the tile earlier (r 4, 4 x
+    // 2,048 windows: 97 and 33 us), so the line is 400.  It goes by the frame
+    // and not by the batch: the two sum in another order, and a pair's
+    // result must not depend on the batch it is in.
+    const bool tile = g.nx * g.ny > 400;
+    if (g.R == 4) return tile ? launch_rows<T, 16, 4, 4, 4, 2, 512>(g, n, s) : launch_rows<T, 16, 4, 1, 1, 8, 320>(g, n, s);
+    if (g.R == 8) return tile ? launch_rows<T, 16, 8, 4, 2, 2, 512>(g, n, s) : launch_rows<T, 16, 8, 1, 1, 8, 576>(g, n, s);
+    if (g.R == 1) return tile ? launch_rows<T, 16, 1, 4, 4, 4, 320>(g, n, s) : launch_rows<T, 16, 1, 1, 1, 16, 192>(g, n, s);
+  }
   return hipErrorInvalidValue;
 }
 
@@ -1678,6 +2204,7 @@ int correct_impl(const Plan& P) {
   if (P.p.dtype == PIV_F32) return 0;
   if (P.p.win != 2 * P.p.step) return 0;
   if ((P.p.step == 8 || P.p.step == 12) && (R == 4 || R == 1)) return 1;
+  if (P.p.step == 16 && (R == 8 || R == 4 || R == 1)) return 1;
   return 0;
 }
 
