@@ -5,6 +5,7 @@
 // exact.  Both passes stream the frames once (reads and writes coalesced by
 // rows); the tile halos of the high-pass come from L2.
 #include <algorithm>
+#include <type_traits>
 
 #include "dev_common.h"
 #include "piv_internal.h"
@@ -15,17 +16,26 @@ namespace {
 // ---------------------------------------------------------------------------
 // High-pass: out = max(0, I - floor(sum / count)) over the image part of the
 // (2r+1)^2 box around each pixel.  One wave owns a strip of columns and a
-// band of rows and walks down it: lane L holds the vertical box sums of the
-// PX pixels of one aligned word (PX = 4 for u8, 2 for u16), updated per row
-// by the row entering and the row leaving the box (each a coalesced word
-// read; the leaving row comes from cache); the wave's sums go through LDS,
-// where each lane adds the 2r+1 columns around its pixels.  The strip's
-// first and last h = ceil(r / PX) lanes only supply sums, so strips overlap
-// by 2h words.  The pixel count of the clipped box is a product of two
-// clipped spans; the quotient comes from a float reciprocal, corrected to
-// the exact floor.
+// band of rows and walks down it: a lane holds the vertical box sums of four
+// pixels (u8: as two pairs of 16-bit fields, a sum is at most 33 x 255),
+// updated per row by the row entering and the row leaving the box.  The sums of the columns around the lane's
+// pixels come from the neighbouring lanes by DPP wave shifts, so rows need no
+// barrier and several are in flight; a lane's last 2r+1 rows wait in its own
+// LDS column for the row's turn at the centre and at leaving, so that every
+// row is read once per band.  Bound by VALU issue (about 45 instructions per
+// four pixels and row, u8) and, at an eighth of the waves a SIMD can hold,
+// latency.  64 x 1 MP u8, r 7: 103 -> 54 us (with word strips, sums through
+// LDS and the leaving and centre rows read again from memory, 3.5 times the
+// frame's bytes); 8 x 4K u16, r 5: 121 -> 68 us.  The strip's first and last
+// h = ceil(r / 4) lanes only supply sums, so strips overlap by 2h lanes.  The
+// pixel count of the clipped box is a product of two clipped spans; the
+// quotient comes from a float reciprocal, corrected to the exact floor.
 // ---------------------------------------------------------------------------
-constexpr int HBAND = 64;
+// Rows of a band: more bands hide latency, each adds 2r rows to read.  r 7,
+// 64 x 1 MP u8: 54 us with 32, 62 with 64, 79 with 128; r 5, 8 x 4K u16: 73,
+// 68 and 86 us.
+template <typename T>
+constexpr int hp_band() { return sizeof(T) == 1 ? 32 : 64; }
 
 // floor(s / c) for quotients below 2^16 (s < 2^27, 1 <= c < 2^11): the
 // float estimate is then within one of the quotient, and integer
@@ -41,44 +51,107 @@ __device__ __forceinline__ uint32_t udiv_small(uint32_t s, uint32_t c) {
   return (uint32_t)q;
 }
 
-// floor(s / d) for the whole box, d = (2R+1)^2, s < 2^27: the product with
-// M = ceil(2^(32+k) / d), k = ceil(log2 d) - 1 (so that M < 2^32), keeps
-// its error s (M d - 2^(32+k)) / d below 2^(32+k) / d > 2^31 > s, hence exact
-template <int D>
+// floor(s / D) for the whole box, D = (2R+1)^2, s <= D * maxval.
+// u16 (s < 2^27): the product with M = ceil(2^(32+k) / D), k = ceil(log2 D) - 1
+// (so that M < 2^32), keeps its error s (M D - 2^(32+k)) / D below
+// 2^(32+k) / D > 2^31 > s, hence exact.  u8 (s < 2^19): the same with a
+// 32-bit product of 24-bit factors at full rate, floor(s M / 2^K) with
+// M = ceil(2^K / D), exact while s (M D - 2^K) < 2^K and s M < 2^32.
+template <int D, bool kByte>
 struct BoxDiv {
   static constexpr int K = []() { int k = 0; while ((1 << (k + 1)) < D) ++k; return k; }();
   static constexpr uint32_t M = (uint32_t)((((uint64_t)1 << (32 + K)) + D - 1) / D);
   static_assert((1ull << K) < (unsigned long long)D && (((uint64_t)1 << (32 + K)) / D) > (1u << 27), "magic range");
+  static constexpr uint64_t SMAX = 255ull * D;
+  static constexpr bool ok(int k) {
+    const uint64_t m = (((uint64_t)1 << k) + D - 1) / D;
+    return SMAX * m < (1ull << 32) && SMAX * (m * D - ((uint64_t)1 << k)) < ((uint64_t)1 << k) && m < (1u << 24);
+  }
+  static constexpr int K8 = []() { int k = 31; while (k > 0 && !ok(k)) --k; return k; }();
+  static constexpr uint32_t M8 = (uint32_t)((((uint64_t)1 << K8) + D - 1) / D);
+  static __device__ __forceinline__ uint32_t div(uint32_t s) {
+    if constexpr (kByte && K8 > 0) return __umul24(s, M8) >> K8;
+    else return __umulhi(s, M) >> K;
+  }
 };
+
+// the value of the lane to the right / left (0 past the wave's ends)
+__device__ __forceinline__ uint32_t from_right(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint32_t from_left(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xF, 0xF, true);
+}
+
+constexpr int floor_div(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
+
+// Horizontal box sums of a lane's four pixels from the vertical sums V of
+// its columns: NF columns per word of V (2: 16-bit fields, 1: 32 bits).
+// Words of the columns -R .. R + 3 around the lane's first are fetched from
+// the lanes around; the columns that all four boxes share are summed once.
+template <int R, int NF>
+__device__ __forceinline__ void box_rows(const uint32_t (&V)[4 / NF], uint32_t (&hs)[4]) {
+  constexpr int NV = 4 / NF;
+  constexpr int lo = floor_div(-R, NF), hi = floor_div(R + 3, NF);   // word range, own words 0 .. NV - 1
+  uint32_t w[hi - lo + 1];
+#pragma unroll
+  for (int m = 0; m < NV && m <= hi; ++m) w[m - lo] = V[m];
+#pragma unroll
+  for (int m = NV; m <= hi; ++m) w[m - lo] = from_right(w[m - NV - lo]);
+#pragma unroll
+  for (int m = -1; m >= lo; --m) w[m - lo] = from_left(m + NV >= 0 ? V[m + NV] : w[m + NV - lo]);
+  auto add = [](uint32_t acc, uint32_t word, bool f0, bool f1) __attribute__((always_inline)) {
+    if constexpr (NF == 1) {
+      return acc + word;
+    } else {
+      typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+      const uint32_t sel = (f0 ? 1u : 0u) | (f1 ? 0x10000u : 0u);
+      return (uint32_t)__builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, word), __builtin_bit_cast(u16x2, sel), acc, false);
+    }
+  };
+  uint32_t common = 0u;
+#pragma unroll
+  for (int m = lo; m <= hi; ++m)
+    if (NF * m >= 3 - R && NF * m + NF - 1 <= R) common = add(common, w[m - lo], true, true);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    uint32_t s = common;
+#pragma unroll
+    for (int m = lo; m <= hi; ++m) {
+      if (NF * m >= 3 - R && NF * m + NF - 1 <= R) continue;
+      const bool f0 = NF * m >= e - R && NF * m <= e + R, f1 = NF == 2 && 2 * m + 1 >= e - R && 2 * m + 1 <= e + R;
+      if (f0 || f1) s = add(s, w[m - lo], f0, f1);
+    }
+    hs[e] = s;
+  }
+}
 
 template <typename T, int R>
 __global__ __launch_bounds__(64) void k_highpass(const uint8_t* __restrict__ in, uint8_t* __restrict__ out,
                                                  int64_t pitch, int64_t stride, int W, int H,
                                                  const uint8_t* mask) {
-  constexpr int ES = (int)sizeof(T), PX = 4 / ES;   // pixels per word
+  constexpr int ES = (int)sizeof(T), NW = ES, PX = 4;   // a lane's words of a row, its pixels
+  constexpr int NF = ES == 1 ? 2 : 1, NV = 4 / NF;
   constexpr int r = R;
-  using Div = BoxDiv<(2 * R + 1) * (2 * R + 1)>;
-  __shared__ uint32_t vbuf[2][64 * PX + 1];          // the wave's vertical sums of a row (two rows alternate)
+  using Div = BoxDiv<(2 * R + 1) * (2 * R + 1), ES == 1>;
+  constexpr int G = 4;                                // rows per group
+  constexpr int N = 2 * R + 1 + G;                   // rows of the ring
+  __shared__ uint32_t ring[N * 64 * NW];
   const int pair = blockIdx.z;
   if (slot_off(mask, pair)) return;
   const int L = threadIdx.x;
   constexpr int h = (r + PX - 1) / PX, nout = 64 - 2 * h;
-  const int word = blockIdx.x * nout + L - h;        // this lane's word column (may lie off the image)
-  const int xa = 4 * word;                           // its byte offset in a row
+  const int x0 = PX * (blockIdx.x * nout + L - h);   // this lane's first pixel (may lie off the image)
+  const int xa = x0 * ES;                            // its byte offset in a row
   const int rowbytes = W * ES;
   const uint8_t* src = in + (int64_t)pair * stride;
-  // the lane's word in a row, zero where it leaves the image (the column
-  // clamp and byte mask are the lane's own, the row's test is uniform)
-  const int xc = min(max(xa, 0), (rowbytes - 1) & ~3);
-  const int valid = rowbytes - xa;
-  const uint32_t keep = (xa < 0 || valid <= 0) ? 0u : (valid >= 4 ? 0xffffffffu : (1u << (8 * (valid & 3))) - 1u);
-  auto row_word = [&](int y) -> uint32_t {
-    const uint32_t ok = (unsigned)y < (unsigned)H ? keep : 0u;
-    return *reinterpret_cast<const uint32_t*>(src + (int64_t)min(max(y, 0), H - 1) * pitch + xc) & ok;
-  };
-  auto px = [&](uint32_t w, int e) -> uint32_t { return ES == 1 ? (w >> (8 * e)) & 0xffu : (w >> (16 * e)) & 0xffffu; };
+  struct RowWords { uint32_t w[NW]; };
+  struct __attribute__((aligned(4))) Wide { uint32_t w[NW]; };
+  // the lane's words of a row, zero outside the image: a strip inside the
+  // row reads them together, one at an edge word by word through masks
+  const bool whole = __all(xa >= 0 && xa + 4 * NW <= rowbytes);
+  const int y_first = blockIdx.y * hp_band<T>(), y_end = min(y_first + hp_band<T>(), H);
   const bool outl = L >= h && L < 64 - h;            // lanes whose pixels are written
-  const int x0 = word * PX;                          // first pixel column of the lane
   uint32_t cx[PX];
   bool fx = true;
 #pragma unroll
@@ -87,95 +160,144 @@ __global__ __launch_bounds__(64) void k_highpass(const uint8_t* __restrict__ in,
     fx = fx && cx[e] == 2 * r + 1;
   }
   // (every written pixel of the strip has its box's full width)
-  const bool full_x = __all(fx || !(L >= h && L < 64 - h));
-  const int ys = blockIdx.y * HBAND, ye = min(ys + HBAND, H);
-  uint32_t V[PX];
+  const bool full_x = __all(fx || !outl);
+  // divisors c = cx (2r + 1) of rows that are not clipped, as a product:
+  // floor(s / c) = floor(s M / 2^(32 + k)), M and k as in BoxDiv (c >= 3)
+  uint32_t lm[PX];
+  int lk[PX];
+  if (!full_x) {
 #pragma unroll
-  for (int e = 0; e < PX; ++e) V[e] = 0u;
-  for (int dy = -r; dy <= r; ++dy) {
-    const uint32_t w = row_word(ys + dy);
-#pragma unroll
-    for (int e = 0; e < PX; ++e) V[e] += px(w, e);
+    for (int e = 0; e < PX; ++e) {
+      const uint32_t c = (uint32_t)max((int)cx[e], 1) * (2 * r + 1);
+      lk[e] = 31 - __builtin_clz(c - 1);
+      lm[e] = (uint32_t)((((uint64_t)1 << (32 + lk[e])) + c - 1) / c);
+    }
   }
   uint8_t* dst = out + (int64_t)pair * stride;
-  // rows in groups of G: the words of the next group (entering, leaving and
-  // centre rows) are requested while this group is worked
-  constexpr int G = 4;
-  uint32_t ci[G], co[G], cc[G], ni[G], no[G], nc[G];
-  auto fetch = [&](int yg, uint32_t* wi, uint32_t* wo, uint32_t* wc) {
+
+  auto strip = [&](auto whole_c) __attribute__((always_inline)) {
+    constexpr bool kWhole = decltype(whole_c)::value;
+    auto row_words = [&](int y) __attribute__((always_inline)) {
+      RowWords o;
+      const uint32_t ok = (unsigned)y < (unsigned)H ? 0xffffffffu : 0u;
+      const uint8_t* row = src + (int64_t)min(max(y, 0), H - 1) * pitch;
+      if constexpr (kWhole) {
+        const Wide v = *reinterpret_cast<const Wide*>(row + xa);
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      wi[g] = row_word(yg + g + r);
-      wo[g] = row_word(yg + g - r - 1);
-      wc[g] = row_word(yg + g);
-    }
-  };
-  fetch(ys, ci, co, cc);
-  for (int yg = ys; yg < ye; yg += G) {
-    if (yg + G < ye) fetch(yg + G, ni, no, nc);
+        for (int k = 0; k < NW; ++k) o.w[k] = v.w[k] & ok;
+      } else {
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int y = yg + g;
-      if (y >= ye) break;
-      if (y > ys) {
-#pragma unroll
-        for (int e = 0; e < PX; ++e) V[e] += px(ci[g], e) - px(co[g], e);
+        for (int k = 0; k < NW; ++k) o.w[k] = masked_word(row, rowbytes, xa + 4 * k) & ok;
       }
-      const uint32_t wc = cc[g];
-      // (rows alternate between two buffers: a row's buffer is written again
-      // two rows later, after the next row's barrier, when every lane has
-      // finished reading it)
-      uint32_t* vb = vbuf[(y - ys) & 1];
+      return o;
+    };
+    auto px = [](const RowWords& w, int e) -> uint32_t {
+      return ES == 1 ? (w.w[0] >> (8 * e)) & 0xffu : (w.w[(e * ES) >> 2] >> (16 * (e & 1))) & 0xffffu;
+    };
+    // the lane's pixels in the layout of V
+    auto fields = [&](const RowWords& w, int m) -> uint32_t {
+      if constexpr (ES == 1) return __builtin_amdgcn_perm(0u, w.w[0], m == 0 ? 0x0c010c00u : 0x0c030c02u);
+      else return px(w, m);
+    };
+    // ring of the lane's words of the last rows (its own LDS column, so the
+    // accesses of a wave need no barrier): row y sits in slot (y - first) mod N
+    auto put = [&](int slot, const RowWords& w) __attribute__((always_inline)) {
 #pragma unroll
-      for (int e = 0; e < PX; ++e) vb[L * PX + e] = V[e];
-      __syncthreads();
-      if (outl) {
-        // box sums of the lane's pixels: the first by 2r+1 columns, then slid
-        const int c0 = L * PX;
-        uint32_t hsum = 0u;
+      for (int k = 0; k < NW; ++k) ring[(slot * 64 + L) * NW + k] = w.w[k];
+    };
+    auto get = [&](int slot) __attribute__((always_inline)) {
+      RowWords w;
 #pragma unroll
-        for (int i = -r; i <= r; ++i) hsum += vb[c0 + i];
-        const uint32_t cy = (uint32_t)(min(y + r, H - 1) - max(y - r, 0) + 1);
-        uint32_t hs[PX];
+      for (int k = 0; k < NW; ++k) w.w[k] = ring[(slot * 64 + L) * NW + k];
+      return w;
+    };
+    auto wrap = [](int slot) { return slot >= N ? slot - N : slot; };
+    // slot 0 holds row y_first - r - 1 (which no box of the band takes)
+    uint32_t V[NV];
 #pragma unroll
-        for (int e = 0; e < PX; ++e) {
-          if (e) hsum += vb[c0 + e + r] - vb[c0 + e - 1 - r];
-          hs[e] = hsum;
+    for (int m = 0; m < NV; ++m) V[m] = 0u;
+    RowWords ci[G], co[G], cc[G], ni[G];
+    constexpr int INIT = 2 * R;   // rows y_first - r .. y_first + r - 1
+#pragma unroll
+    for (int d0 = 0; d0 < INIT; d0 += 8) {
+      RowWords w[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (d0 + k < INIT) w[k] = row_words(y_first - r + d0 + k);
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (d0 + k < INIT) {
+          put(1 + d0 + k, w[k]);
+#pragma unroll
+          for (int m = 0; m < NV; ++m) V[m] += fields(w[k], m);
         }
-        uint32_t m[PX];
-        if (cy == 2 * r + 1 && full_x) {
+    }
+#pragma unroll
+    for (int k = 0; k < NW; ++k) ring[L * NW + k] = 0u;
+    auto fetch = [&](int yg, RowWords (&wi)[G]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int k = 0; k < G; ++k) wi[k] = row_words(yg + k + r);
+    };
+    fetch(y_first, ci);
+    int base = 0;   // slot of row yg - r - 1
+    for (int yg = y_first; yg < y_end; yg += G) {
+      if (yg + G < y_end) fetch(yg + G, ni);
+      // (the ring holds rows yg - r - 1 .. yg + G - 1 + r)
+#pragma unroll
+      for (int k = 0; k < G; ++k) put(wrap(base + 2 * R + 1 + k), ci[k]);
+#pragma unroll
+      for (int k = 0; k < G; ++k) co[k] = get(wrap(base + k));
+#pragma unroll
+      for (int k = 0; k < G; ++k) cc[k] = get(wrap(base + R + 1 + k));
+      base = wrap(base + G);
+#pragma unroll
+      for (int k = 0; k < G; ++k) {
+        const int y = yg + k;
+        if (y >= y_end) break;
+        // (every field ends in range, so the fields' sums do not mix)
+#pragma unroll
+        for (int m = 0; m < NV; ++m) V[m] = V[m] + fields(ci[k], m) - fields(co[k], m);
+        uint32_t hs[PX], o[PX];
+        box_rows<R, NF>(V, hs);
+        const uint32_t cy = (uint32_t)(min(y + r, H - 1) - max(y - r, 0) + 1);
+        if (cy == 2 * r + 1 && !full_x) {
+          // boxes clipped at the left or right: the lane's own divisors
+#pragma unroll
+          for (int e = 0; e < PX; ++e)
+            o[e] = __builtin_elementwise_sub_sat(px(cc[k], e), __umulhi(hs[e], lm[e]) >> lk[e]);
+        } else if (cy == 2 * r + 1) {
           // the whole box inside the image (the usual case, taken by the
           // whole wave): the constant divisor's product
 #pragma unroll
-          for (int e = 0; e < PX; ++e) m[e] = __umulhi(hs[e], Div::M) >> Div::K;
+          for (int e = 0; e < PX; ++e) o[e] = __builtin_elementwise_sub_sat(px(cc[k], e), Div::div(hs[e]));
         } else {
 #pragma unroll
-          for (int e = 0; e < PX; ++e) m[e] = udiv_small(hs[e], cx[e] * cy);
+          for (int e = 0; e < PX; ++e) o[e] = __builtin_elementwise_sub_sat(px(cc[k], e), udiv_small(hs[e], max(cx[e], 1u) * cy));
         }
-        uint32_t o[PX];
+        if (outl) {
+          T* orow = reinterpret_cast<T*>(dst + (int64_t)y * pitch);
+          if (kWhole || (x0 >= 0 && x0 + PX <= W)) {
+            Wide v;
+            if constexpr (ES == 1) {
+              v.w[0] = o[0] | (o[1] << 8) | (o[2] << 16) | (o[3] << 24);
+            } else {
+              v.w[0] = o[0] | (o[1] << 16);
+              v.w[NW - 1] = o[2] | (o[3] << 16);
+            }
+            *reinterpret_cast<Wide*>(orow + x0) = v;
+          } else {
 #pragma unroll
-        for (int e = 0; e < PX; ++e) {
-          const uint32_t I = px(wc, e);
-          o[e] = I > m[e] ? I - m[e] : 0u;
-        }
-        T* orow = reinterpret_cast<T*>(dst + (int64_t)y * pitch);
-        if (x0 >= 0 && x0 + PX <= W) {
-          if constexpr (ES == 1) *reinterpret_cast<uint32_t*>(orow + x0) = o[0] | (o[1] << 8) | (o[2] << 16) | (o[3] << 24);
-          else *reinterpret_cast<uint32_t*>(orow + x0) = o[0] | (o[1] << 16);
-        } else {
-#pragma unroll
-          for (int e = 0; e < PX; ++e)
-            if (x0 + e >= 0 && x0 + e < W) orow[x0 + e] = (T)o[e];
+            for (int e = 0; e < PX; ++e)
+              if (x0 + e >= 0 && x0 + e < W) orow[x0 + e] = (T)o[e];
+          }
         }
       }
-    }
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      ci[g] = ni[g];
-      co[g] = no[g];
-      cc[g] = nc[g];
+      for (int k = 0; k < G; ++k) ci[k] = ni[k];
     }
-  }
+  };
+  if (whole) strip(std::true_type());
+  else strip(std::false_type());
 }
 
 // ---------------------------------------------------------------------------
@@ -489,10 +611,10 @@ int clahe_bins(const Plan& P) {
 }
 
 hipError_t launch_highpass(const Plan& P, const void* in, void* out, int64_t pitch, int n, int r, hipStream_t s) {
-  const int px = P.es == 1 ? 4 : 2;
-  const int nout = 64 - 2 * ((r + px - 1) / px);       // words written per strip
-  const int words = (P.p.width + px - 1) / px;
-  dim3 grid((words + nout - 1) / nout, (P.p.height + HBAND - 1) / HBAND, n);
+  const int nout = 64 - 2 * ((r + 3) / 4);             // groups of four pixels written per strip
+  const int words = (P.p.width + 3) / 4;
+  const int band = P.es == 1 ? hp_band<uint8_t>() : hp_band<uint16_t>();
+  dim3 grid((words + nout - 1) / nout, (P.p.height + band - 1) / band, n);
   const int64_t stride = pitch * P.p.height;
   const uint8_t* i8 = (const uint8_t*)in;
   uint8_t* o8 = (uint8_t*)out;
