@@ -70,7 +70,7 @@ struct BoxDiv {
   static constexpr int K8 = []() { int k = 31; while (k > 0 && !ok(k)) --k; return k; }();
   static constexpr uint32_t M8 = (uint32_t)((((uint64_t)1 << K8) + D - 1) / D);
   static __device__ __forceinline__ uint32_t div(uint32_t s) {
-    if constexpr (kByte && K8 > 0) return __umul24(s, M8) >> K8;
+    if constexpr (kByte && K8 > 0) return (uint32_t)__umul24(s, M8) >> K8;   // (declared to return int)
     else return __umulhi(s, M) >> K;
   }
 };
