@@ -477,7 +477,8 @@ __global__ __launch_bounds__(NT) void k_clahe_lut(const uint8_t* __restrict__ in
   }
 }
 
-// CLAHE, pass 2: every pixel blends the mappings of the (up to) four tiles
+// CLAHE, pass 2 for small u8 tiles and blends beyond 32 bits (the other
+// cases: k_clahe_cells below): every pixel blends the mappings of the (up to) four tiles
 // whose centres surround it.  In doubled coordinates (centres may be
 // half-integers) the tile holding x is k = ceil((x+1) tx / W) - 1 and the
 // centre at or left of 2x is k or k - 1; before the first centre or after
@@ -663,6 +664,168 @@ __global__ __launch_bounds__(256) void k_clahe_map(const uint8_t* in, uint8_t* o
   }
 }
 
+// CLAHE, pass 2, by cells: the frame falls into (tx + 1) x (ty + 1) cells
+// bounded by the tile centres, and all pixels of a cell blend the same four
+// mappings over the same denominators.  A workgroup takes a band of rows of
+// one cell: it lays the four mappings in LDS as one 8-byte entry per bin
+// (one read per pixel), its threads take groups of four pixels in order, U
+// of them requested together, and the division by the cell's constant is a
+// shift or a product.  The weights are linear in x and y, both of a pair in
+// one word.  Every pixel is read and written by one thread, bytes of another
+// cell in a group are left alone, so the pass may run in place.
+// kTop16: the horizontal blends fit 16 bits, so both halves of the blend are
+// 16-bit dot products; otherwise they are products of 24-bit factors (both
+// checked on the host, as is that the numerator fits 32 bits).
+// 64 x 1 MP u8 on 8 x 8 tiles: 85 -> 45 us, 8 x 4K u16 on 7 x 5 tiles: 187
+// -> 72 us (the kernel above: a table of column constants per thread, four reads per pixel
+// from the staged (u8) or global (u16) mappings, full 32- or 64-bit products).
+struct CellAxis {
+  int lo, hi;   // pixels [lo, hi)
+  int ta, tb;   // the two tiles
+  int w0, d;    // weight of tb at pixel x: (2 x - w0) / d
+};
+// cell k of an axis: between the centres of tiles k - 1 and k
+__device__ __forceinline__ CellAxis clahe_cell(int k, int L, int n) {
+  CellAxis r;
+  // the first pixel at or right of tile a's centre (e(a) + e(a+1) - 1) / 2
+  auto start = [&](int a) { return (tile_edge(a, L, n) + tile_edge(a + 1, L, n)) >> 1; };
+  r.lo = k == 0 ? 0 : start(k - 1);
+  r.hi = k == n ? L : start(k);
+  if (k == 0 || k == n) {
+    r.ta = r.tb = k == 0 ? 0 : n - 1;
+    r.w0 = 0;
+    r.d = 0;   // (one tile: the weights are constant, see below)
+  } else {
+    r.ta = k - 1;
+    r.tb = k;
+    r.w0 = tile_edge(k - 1, L, n) + tile_edge(k, L, n) - 1;
+    r.d = tile_edge(k + 1, L, n) - tile_edge(k - 1, L, n);
+  }
+  return r;
+}
+
+template <typename T, int NT, int NB, int SH, bool kTop16>
+__global__ __launch_bounds__(NT) void k_clahe_cells(const uint8_t* in, uint8_t* out, int64_t pitch, int64_t stride,
+                                                    int W, int H, int tx, int ty, int bands, int band_rows,
+                                                    const uint16_t* __restrict__ lut, const uint8_t* mask) {
+  constexpr int ES = (int)sizeof(T), NW = ES;   // words of a group of four pixels
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  __shared__ __align__(16) uint2 s_lut[NB];     // {top left | top right << 16, bottom left | bottom right << 16}
+  const int pair = blockIdx.z;
+  if (slot_off(mask, pair)) return;
+  const int t = threadIdx.x;
+  const int ky = blockIdx.y / bands, band = blockIdx.y - ky * bands;
+  const CellAxis cx = clahe_cell(blockIdx.x, W, tx), cy = clahe_cell(ky, H, ty);
+  const int y_lo = cy.lo + band * band_rows, y_hi = min(y_lo + band_rows, cy.hi);
+  if (cx.lo >= cx.hi || y_lo >= y_hi) return;   // (the whole workgroup)
+  {
+    const uint16_t* Lp = lut + (int64_t)pair * ty * tx * NB;
+    const uint32_t* q00 = reinterpret_cast<const uint32_t*>(Lp + ((int64_t)cy.ta * tx + cx.ta) * NB);
+    const uint32_t* q01 = reinterpret_cast<const uint32_t*>(Lp + ((int64_t)cy.ta * tx + cx.tb) * NB);
+    const uint32_t* q10 = reinterpret_cast<const uint32_t*>(Lp + ((int64_t)cy.tb * tx + cx.ta) * NB);
+    const uint32_t* q11 = reinterpret_cast<const uint32_t*>(Lp + ((int64_t)cy.tb * tx + cx.tb) * NB);
+    for (int k = t; k < NB / 2; k += NT) {   // two bins of each mapping a word
+      const uint32_t a = q00[k], b = q01[k], c = q10[k], d = q11[k];
+      s_lut[2 * k] = make_uint2((a & 0xffffu) | (b << 16), (c & 0xffffu) | (d << 16));
+      s_lut[2 * k + 1] = make_uint2((a >> 16) | (b & 0xffff0000u), (c >> 16) | (d & 0xffff0000u));
+    }
+  }
+  // weights as (d - w) | w << 16 with w = 2 x - w0; an edge cell's are 1 | 0,
+  // and 2 | 0 across where that leaves the denominator 1 (the rounded
+  // quotient of twice numerator and denominator is the same)
+  const int dy = cy.d ? cy.d : 1, dx = cx.d ? cx.d : (dy == 1 ? 2 : 1);
+  const uint32_t wx_c = cx.d ? (uint32_t)(cx.d + cx.w0) - ((uint32_t)cx.w0 << 16) : (uint32_t)dx;
+  const uint32_t wy_c = cy.d ? (uint32_t)(cy.d + cy.w0) - ((uint32_t)cy.w0 << 16) : 1u;
+  const uint32_t wstep = 0x20000u - 2u;                  // per pixel
+  const uint32_t wx_s = cx.d ? wstep : 0u, wy_s = cy.d ? wstep : 0u;
+  const uint32_t den = (uint32_t)dx * (uint32_t)dy, half = den / 2;
+  // floor(n2 / den), den >= 2: n2 M / 2^(32 + k), M = ceil(2^(32 + k) / den),
+  // k = ceil(log2 den) - 1, is exact for n2 < 2^31 (its error n2 (M den -
+  // 2^(32+k)) / den stays below 2^(32+k) / den) and else at most one too large
+  const int kd = 31 - __builtin_clz(den - 1);
+  const uint32_t md = (uint32_t)((((uint64_t)1 << (32 + kd)) + den - 1) / den);
+  const bool pow2 = (den & (den - 1)) == 0;
+  __syncthreads();
+
+  const uint8_t* src = in + (int64_t)pair * stride;
+  uint8_t* dst = out + (int64_t)pair * stride;
+  const int g0 = cx.lo >> 2, ng = ((cx.hi + 3) >> 2) - g0, items = ng * (y_hi - y_lo);
+  const int srow = NT / ng, scol = NT - srow * ng;   // one step of NT groups
+  int ry = t / ng, rc = t - ry * ng;                 // the thread's next group
+  constexpr int U = 4;
+  struct __attribute__((aligned(4))) Group { uint32_t w[NW]; };
+  auto cell = [&](auto pow2_c) __attribute__((always_inline)) {
+    for (int p0 = t; p0 < items; p0 += U * NT) {
+      Group v[U];
+      int gx[U], gy[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        gx[u] = 4 * (g0 + rc);
+        gy[u] = min(y_lo + ry, y_hi - 1);
+        const uint8_t* row = src + (int64_t)gy[u] * pitch;
+        if (gx[u] + 4 <= W) {
+          v[u] = *reinterpret_cast<const Group*>(row + gx[u] * ES);
+        } else {
+#pragma unroll
+          for (int k = 0; k < NW; ++k) v[u].w[k] = masked_word(row, W * ES, gx[u] * ES + 4 * k);
+        }
+        ry += srow;
+        rc += scol;
+        if (rc >= ng) {
+          rc -= ng;
+          ++ry;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (p0 + u * NT >= items) break;
+        const uint32_t wy = wy_c + (uint32_t)gy[u] * wy_s;
+        uint32_t wx = wx_c + (uint32_t)gx[u] * wx_s;
+        uint32_t o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t px = ES == 1 ? (v[u].w[0] >> (8 * e)) & 0xffu : (v[u].w[(e * ES) >> 2] >> (16 * (e & 1))) & 0xffffu;
+          const uint2 l = s_lut[(px >> SH) & (NB - 1)];
+          const uint32_t top = (uint32_t)__builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, l.x),
+                                                                __builtin_bit_cast(u16x2, wx), 0u, false);
+          const uint32_t bot = (uint32_t)__builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, l.y),
+                                                                __builtin_bit_cast(u16x2, wx), 0u, false);
+          uint32_t n2;
+          if constexpr (kTop16)
+            n2 = (uint32_t)__builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, top | (bot << 16)),
+                                                  __builtin_bit_cast(u16x2, wy), half, false);
+          else
+            n2 = (uint32_t)__umul24(top, wy & 0xffffu) + (uint32_t)__umul24(bot, wy >> 16) + half;
+          if constexpr (decltype(pow2_c)::value) {
+            o[e] = n2 >> (kd + 1);
+          } else {
+            o[e] = __umulhi(n2, md) >> kd;
+            if constexpr (!kTop16) o[e] -= o[e] * den > n2 ? 1u : 0u;
+          }
+          wx += wx_s;
+        }
+        T* orow = reinterpret_cast<T*>(dst + (int64_t)gy[u] * pitch);
+        if (gx[u] >= cx.lo && gx[u] + 4 <= cx.hi) {
+          Group w;
+          if constexpr (ES == 1) {
+            w.w[0] = o[0] | (o[1] << 8) | (o[2] << 16) | (o[3] << 24);
+          } else {
+            w.w[0] = o[0] | (o[1] << 16);
+            w.w[NW - 1] = o[2] | (o[3] << 16);
+          }
+          *reinterpret_cast<Group*>(orow + gx[u]) = w;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (gx[u] + e >= cx.lo && gx[u] + e < cx.hi) orow[gx[u] + e] = (T)o[e];
+        }
+      }
+    }
+  };
+  if (pow2) cell(std::true_type());
+  else cell(std::false_type());
+}
+
 }  // namespace
 
 int clahe_bins(const Plan& P) {
@@ -710,40 +873,72 @@ hipError_t launch_clahe(const Plan& P, const void* in, void* out, int64_t pitch,
   const int bits = P.p.dtype == PIV_U8 ? 8 : P.p.bit_depth;
   const int nbins = clahe_bins(P), shift = bits - (bits < 12 ? bits : 12), maxval = (1 << bits) - 1;
   const int64_t stride = pitch * P.p.height;
+  const uint8_t* i8 = (const uint8_t*)in;
+  uint8_t* o8 = (uint8_t*)out;
   dim3 g1(tx, ty, n);
-  dim3 g2((P.p.width + MQ - 1) / MQ, (P.p.height + MR - 1) / MR, n);
-  const bool staged = clahe_stage_fits(P, tx, ty, nbins);
+#define PIV_LUT(T_, NT_, NH_, HB_, SH_)                                                                                \
+  hipLaunchKernelGGL((k_clahe_lut<T_, NT_, NH_, HB_, SH_>), g1, dim3(NT_), 0, s, i8, pitch, stride, P.p.width, P.p.height, \
+                     tx, ty, nbins, maxval, clip_factor, lut, P.slot_mask)
+  if (P.es == 1) PIV_LUT(uint8_t, 256, 8, 256, 0);
+  else if (shift == 0) PIV_LUT(uint16_t, 1024, 2, 4096, 0);
+  else PIV_LUT(uint16_t, 1024, 2, 4096, 4);   // 16 bits in 4096 bins
+#undef PIV_LUT
+  if (hipError_t e = hipGetLastError()) return e;
   // the blend denominator per axis is a centre distance in doubled
-  // coordinates, e(a+2) - e(a); the 32-bit path needs
-  // maxval dx dy + dx dy / 2 < 2^24 for the largest ones
+  // coordinates, e(a+2) - e(a)
   auto dmax = [](int L, int n) {
-    int64_t m = 1;
+    int64_t m = 2;
     for (int a = 0; a + 2 <= n; ++a) m = std::max<int64_t>(m, (int64_t)(a + 2) * L / n - (int64_t)a * L / n);
     return m;
   };
-  const int64_t dd = dmax(P.p.width, tx) * dmax(P.p.height, ty);
-  const bool narrow = (int64_t)maxval * dd + dd / 2 < (int64_t(1) << 24);
-#define PIV_MAP(T_, ST_, NA_)                                                                              \
-  hipLaunchKernelGGL((k_clahe_map<T_, ST_, NA_>), g2, dim3(256), 0, s, (const uint8_t*)in, (uint8_t*)out, pitch, \
-                     stride, P.p.width, P.p.height, tx, ty, nbins, shift, (const uint16_t*)lut, P.slot_mask)
-#define PIV_CLAHE(T_, NT_, NH_, HB_, SH_)                                                                          \
-  hipLaunchKernelGGL((k_clahe_lut<T_, NT_, NH_, HB_, SH_>), g1, dim3(NT_), 0, s, (const uint8_t*)in, pitch, stride, P.p.width, \
-                     P.p.height, tx, ty, nbins, maxval, clip_factor, lut, P.slot_mask);                  \
-  if (hipError_t e = hipGetLastError()) return e;                                                              \
-  if (staged && narrow) PIV_MAP(T_, true, true);                                                                \
-  else if (staged) PIV_MAP(T_, true, false);                                                                    \
-  else if (narrow) PIV_MAP(T_, false, true);                                                                    \
-  else PIV_MAP(T_, false, false)
-  if (P.es == 1) {
-    PIV_CLAHE(uint8_t, 256, 8, 256, 0);
-  } else {
-    if (shift == 0) {
-      PIV_CLAHE(uint16_t, 1024, 2, 4096, 0);
-    } else {
-      PIV_CLAHE(uint16_t, 1024, 2, 4096, 4);   // 16 bits in 4096 bins
+  const int64_t dxm = dmax(P.p.width, tx), dd = dxm * dmax(P.p.height, ty);
+  // By cells where numerators, and the quotient times its denominator, fit 32
+  // bits, and for u8 while a tile has 1,024 pixels or more: a cell lays all
+  // bins of its mappings in LDS whatever its size (16 x 1 MP u8, both passes:
+  // 28 against 38 us at tiles of 128 x 128, 41 and 70 at 64 x 64, 109 and 107
+  // at 32 x 32, 392 and 239 at 16 x 16; u16 is faster by cells down to 30 x
+  // 17, 439 and 500 us).
+  if ((maxval + 2) * dd < (int64_t(1) << 32) && maxval * dxm < (1 << 24) &&
+      (P.es == 2 || (int64_t)P.p.width * P.p.height >= (int64_t)1024 * tx * ty)) {
+    const bool top16 = maxval * dxm < 65536 && (maxval + 1) * dd < (int64_t(1) << 31);
+    auto cell_max = [](int L, int n) {   // the largest extent of a cell
+      auto start = [&](int a) { return (int)(((int64_t)a * L / n + (int64_t)(a + 1) * L / n) >> 1); };
+      int m = std::max(start(0), L - start(n - 1));
+      for (int a = 1; a < n; ++a) m = std::max(m, start(a) - start(a - 1));
+      return m;
+    };
+    // pixels of a workgroup: enough to pay for its mappings (2 and 32 KB);
+    // half as many u8, or twice as many u16, take 17% and 7% longer
+    const int rows = cell_max(P.p.height, ty), target = P.es == 1 ? 16384 : 32768;
+    const int band_rows = std::min(rows, std::max(8, target / cell_max(P.p.width, tx)));
+    const int bands = (rows + band_rows - 1) / band_rows;
+    dim3 gc(tx + 1, (ty + 1) * bands, n);
+#define PIV_CELLS(T_, NT_, NB_, SH_, TOP_)                                                                              \
+  hipLaunchKernelGGL((k_clahe_cells<T_, NT_, NB_, SH_, TOP_>), gc, dim3(NT_), 0, s, i8, o8, pitch, stride, P.p.width,     \
+                     P.p.height, tx, ty, bands, band_rows, (const uint16_t*)lut, P.slot_mask)
+    if (P.es == 1) {
+      if (top16) PIV_CELLS(uint8_t, 256, 256, 0, true);
+      else PIV_CELLS(uint8_t, 256, 256, 0, false);
+    } else if (shift == 0) {
+      if (top16) PIV_CELLS(uint16_t, 512, 4096, 0, true);
+      else PIV_CELLS(uint16_t, 512, 4096, 0, false);
+    } else {   // (16-bit values: a blend over two pixels or more leaves 16 bits)
+      PIV_CELLS(uint16_t, 512, 4096, 4, false);
     }
+#undef PIV_CELLS
+    return hipGetLastError();
   }
-#undef PIV_CLAHE
+  dim3 g2((P.p.width + MQ - 1) / MQ, (P.p.height + MR - 1) / MR, n);
+  // small u8 tiles (their numerators stay below 2^24), and blends beyond 32 bits
+  const bool staged = clahe_stage_fits(P, tx, ty, nbins), narrow = maxval * dd + dd / 2 < (int64_t(1) << 24);
+#define PIV_MAP(T_, ST_, NA_)                                                                                           \
+  hipLaunchKernelGGL((k_clahe_map<T_, ST_, NA_>), g2, dim3(256), 0, s, i8, o8, pitch, stride, P.p.width, P.p.height, tx, \
+                     ty, nbins, shift, (const uint16_t*)lut, P.slot_mask)
+  if (P.es == 2) PIV_MAP(uint16_t, false, false);
+  else if (staged && narrow) PIV_MAP(uint8_t, true, true);
+  else if (narrow) PIV_MAP(uint8_t, false, true);
+  else if (staged) PIV_MAP(uint8_t, true, false);
+  else PIV_MAP(uint8_t, false, false);
 #undef PIV_MAP
   return hipGetLastError();
 }
