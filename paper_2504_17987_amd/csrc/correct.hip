@@ -6,8 +6,10 @@
 // Implementations of the same definition:
 //  * k_correct_generic -- one workgroup per window; any window/step/radius.
 //  * k_correct_rows    -- 32 px windows at 50% overlap (below).
-//  * k_correct_bands   -- 16 and 24 px windows at 50% overlap, frame B
-//    deformed (below).
+//  * k_correct_bands   -- 16 px windows at 50% overlap, frame B deformed
+//    (below).
+//  * k_correct_halves  -- 24 px windows (u16) with frame B deformed, 16 px
+//    windows with both (below).
 //  * k_correct_tiled   -- the other cases of 50%-overlap windows (win = 2 step):
 //    a workgroup owns a TW x TH tile of windows; the deformed B' tile and the
 //    A tile live in LDS; each thread correlates one step x step cell with a
@@ -1090,9 +1092,7 @@ struct BandCfg {
   static constexpr int BW4 = (BW + 3) / 4 * 4;            // B' columns written (whole groups)
   static constexpr int TAB_WORDS = 2 * (BH + BW4);
   static constexpr int RES_WORDS = NWIN * NS + 2 * NG * NWIN;
-  // raw source box of B (words): at step 8 a 3888-word box; at step 12 room
-  // for a predictor range of 16 px across the tile (u16 rows)
-  static constexpr int RAW_WORDS = STEP == 8 ? 3888 : ((BW + 19) * 2 / 4 + 2) * (BH + 19);
+  static constexpr int RAW_WORDS = 3888;   // raw source box of B
   static constexpr int UNION = RAW_WORDS + TAB_WORDS > RES_WORDS ? RAW_WORDS + TAB_WORDS : RES_WORDS;
   static_assert(NC <= 64, "a cell per lane");
   static_assert(NSY % SYG == 0, "shift rows must split evenly");
@@ -1100,7 +1100,7 @@ struct BandCfg {
 };
 
 template <typename T, int STEP, int R, int SYG, int TW, int TH>
-__global__ __launch_bounds__(64 * ((2 * R + 1) / SYG)) __attribute__((amdgpu_waves_per_eu(STEP == 8 ? 3 : 2)))
+__global__ __launch_bounds__(64 * ((2 * R + 1) / SYG)) __attribute__((amdgpu_waves_per_eu(3)))
 void k_correct_bands(CorrArgs g) {
   using C = BandCfg<STEP, R, SYG, TW, TH>;
   constexpr int NT = 64 * C::NG;
@@ -1234,8 +1234,8 @@ void k_correct_bands(CorrArgs g) {
     const int rstep = NT / nwords;
     const int r0 = t / nwords, w = t - r0 * nwords;
     // reads in flight per thread: enough for the whole box in one round
-    // (about 9 rows per thread at step 8 u8, 33 at step 12 u16)
-    constexpr int U = STEP == 8 ? 12 : 36;
+    // (about 9 rows per thread for u8)
+    constexpr int U = 12;
     const bool inside = off32 && iy0 >= 0 && iy0 + nrows <= g.H && xw0 >= 0 && 4 * (xw0 + nwords) <= rowbytes;
     if (r0 < rstep) {
       // slots past the box take its last row again (the same word is
@@ -1436,10 +1436,6 @@ void k_correct_bands(CorrArgs g) {
       saa += s_asum[1][q][lane];
     }
   }
-  // (with large cells the S/Q column sums take a second pass over the band's
-  // rows, after the products, so that their registers and the A cell's are
-  // never live together)
-  constexpr bool kSplitSQ = STEP > 8;
   const float* bbase = sB + (ci * STEP + band * SYG) * C::BP + cj * STEP;
   float cs[BRW], cq[BRW];
   {
@@ -1447,10 +1443,8 @@ void k_correct_bands(CorrArgs g) {
     for (int k = 0; k < SYG; ++k)
 #pragma unroll
       for (int j = 0; j < C::NSY; ++j) Pacc[k][j] = 0.0f;
-    if constexpr (!kSplitSQ) {
 #pragma unroll
-      for (int x = 0; x < BRW; ++x) cs[x] = cq[x] = 0.0f;
-    }
+    for (int x = 0; x < BRW; ++x) cs[x] = cq[x] = 0.0f;
     // stream the B' rows of the band once each; B' row rb meets A row
     // rb - k for shift row k, so the last SYG A rows are kept (converted)
     float ar[SYG][STEP];
@@ -1467,12 +1461,10 @@ void k_correct_bands(CorrArgs g) {
           const uint32_t px = ES == 1 ? (wd >> (8 * (x & 3))) & 0xffu : (wd >> (16 * (x & 1))) & 0xffffu;
           an[x] = (float)px;   // raw A: the offset K enters through the mean below
         }
-        if constexpr (!kSplitSQ) {
 #pragma unroll
-          for (int x = 0; x < BRW; ++x) {
-            cs[x] += brow[x];
-            cq[x] += brow[x] * brow[x];
-          }
+        for (int x = 0; x < BRW; ++x) {
+          cs[x] += brow[x];
+          cq[x] += brow[x] * brow[x];
         }
       }
 #pragma unroll
@@ -1488,20 +1480,6 @@ void k_correct_bands(CorrArgs g) {
             Pacc[k][j] = s;
           }
         }
-      }
-    }
-  }
-  if constexpr (kSplitSQ) {
-    // column sums of the band's first STEP rows
-#pragma unroll
-    for (int x = 0; x < BRW; ++x) cs[x] = cq[x] = 0.0f;
-#pragma unroll
-    for (int rb = 0; rb < STEP; ++rb) {
-#pragma unroll
-      for (int x = 0; x < BRW; ++x) {
-        const float b = bbase[rb * C::BP + x];
-        cs[x] += b;
-        cq[x] += b * b;
       }
     }
   }
@@ -1610,13 +1588,9 @@ void k_correct_bands(CorrArgs g) {
   }
   __syncthreads();
   // ---- peak over the bands, fit, composition with the predictor's window mean
-  // (with large cells, whose kernel has two workgroups per CU and is bound
-  // by latency, the windows are dealt to the waves so that the fits of a
-  // tile run side by side; with small cells, where VALU issue bounds the
-  // kernel, one wave fits them all and the others end)
-  constexpr int WPW = STEP > 8 ? (C::NWIN + C::NG - 1) / C::NG : C::NWIN;   // windows per wave
-  const int wt = band * WPW + lane;
-  if (lane < WPW && wt < C::NWIN) {
+  // (VALU issue bounds the kernel: one wave fits them all and the others end)
+  const int wt = t;
+  if (t < C::NWIN) {
     const int wi = wt / TW, wj = wt - (wt / TW) * TW;
     const int a = a0 + wi, b = b0 + wj;
     if (a < g.ny && b < g.nx) {
@@ -1644,6 +1618,627 @@ void k_correct_bands(CorrArgs g) {
       float pu = 0.0f, pv = 0.0f;
       if (Pn) window_mean_half_overlap(a, b, g.nx, g.ny, node, pu, pv);
       finish_vector(g, pair, a, b, sy, sx, allflat, pu, pv, rhof);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Two waves per shift band (win = 2 step, r 4): the band kernel above for
+// 24 px windows, and for 16 px windows with both frames deformed (kCentral),
+// whose LDS lets a CU hold two workgroups.  Three waves each would leave
+// SIMDs with one wave.  The waves of a band share its shifts by columns (4
+// and 5 of the 9), and of the box sums of B' one takes S and the other Q for
+// all nine; what the other needs passes through LDS per window.  The packed
+// A cells wait in LDS over the raw box (with kCentral A', as floats, in LDS
+// of its own), so that a wave stays within 128 registers and four fit a
+// SIMD.  Two more waves share the staging, the deformation and the fits:
+// with six a SIMD would hold two waves of a workgroup or one, and a launch
+// of 384 threads runs 15% (24 px) and 4% (central) longer.  What bounds it
+// now is VALU issue (24 px: 450 of 524 us; central 131 of 175 us), beside it
+// latency.  Every sum runs in the band kernel's order.  8 x 4K u16, 24 px
+// windows: 606 -> 524 us (three waves with the A cell in 72 of 256
+// registers, 9 spilled); 16 x 1000 x 760 u8 central: 215 -> 175 us
+// (k_correct_tiled).
+// ---------------------------------------------------------------------------
+template <int N>
+using Int = std::integral_constant<int, N>;
+
+template <typename T, int STEP, int TW, int TH, bool kCentral>
+struct HalvesCfg {
+  static constexpr int ES = (int)sizeof(T), R = 4, SYG = 3;
+  static constexpr int CW = TW + 1, CH = TH + 1, NC = CW * CH, NWIN = TW * TH;
+  static constexpr int NSY = 2 * R + 1, NS = NSY * NSY, NG = NSY / SYG;
+  static constexpr int H0 = 4, H1 = NSY - H0;             // shift columns of the two waves of a band
+  static constexpr int NT = 512;
+  static constexpr int AW = CW * STEP, AH = CH * STEP;
+  static constexpr int BW = AW + 2 * R, BH = AH + 2 * R;
+  static constexpr int BP = (BW + 3) / 4 * 4 + 4, AP = AW + 4;   // LDS row pitches (floats)
+  static constexpr int NNX = BW / STEP + 4, NNY = BH / STEP + 3;
+  static constexpr int TAB_WORDS = 2 * (BH + BW);
+  // union: raw source box and interpolation tables while the tiles are
+  // deformed; then what a wave of a band hands the other (S of H1 columns, Q
+  // of H0 per window), and behind it the coefficients and the waves' peaks
+  // (over the packed A cells, which the products read)
+  static constexpr int XW = NG * NWIN * SYG * NSY;
+  static constexpr int CP = STEP * (STEP * ES / 4) + 4;   // words per packed cell (rows of whole words)
+  static constexpr int AW_WORDS = kCentral ? 0 : 64 * CP;
+  static constexpr int RES0 = NWIN * NS + 4 * NG * NWIN;
+  static constexpr int RES_WORDS = XW + (RES0 > AW_WORDS ? RES0 : AW_WORDS);
+  static constexpr int RAW_WORDS = STEP == 8 ? 3888 : ((BW + 19) * 2 / 4 + 2) * (BH + 19);
+  static constexpr int UNION = RAW_WORDS + TAB_WORDS > RES_WORDS ? RAW_WORDS + TAB_WORDS : RES_WORDS;
+  static constexpr int A_WORDS = kCentral ? AH * AP : 0;
+  static constexpr int LDS_WORDS = BH * BP + A_WORDS + UNION + 2 * NNY * NNX + 2 * NG * 64 + NT / 64;
+  static_assert(NC <= 64 && BW % 4 == 0 && STEP % 4 == 0 && R % 4 == 0, "a cell per lane; whole groups of four pixels");
+};
+
+template <typename T, int STEP, int TW, int TH, bool kCentral>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+void k_correct_halves(CorrArgs g) {
+  using C = HalvesCfg<T, STEP, TW, TH, kCentral>;
+  constexpr int NT = C::NT, ES = C::ES, R = C::R, SYG = C::SYG, NSY = C::NSY;
+  constexpr int NWR = STEP * ES / 4;   // words per cell row
+  static_assert(NT == 512 && ((STEP / 2) * ES) % 4 == 0 && (STEP * ES) % 4 == 0, "cell rows are whole aligned words");
+  // (all LDS is dynamic: told of 80 KB, the compiler reserves the registers
+  // of the four waves a SIMD then holds as if no other workgroup fitted)
+  extern __shared__ __align__(16) float s_dyn[];
+  float* const sB = s_dyn;
+  float* const sA = sB + C::BH * C::BP;
+  float* const s_un = sA + C::A_WORDS;
+  float(*const s_node)[C::NNY][C::NNX] = reinterpret_cast<float(*)[C::NNY][C::NNX]>(s_un + C::UNION);
+  // cell sums of A - K and its square, rows dealt to the bands
+  float(*const s_asum)[C::NG][64] = reinterpret_cast<float(*)[C::NG][64]>(s_un + C::UNION + 2 * C::NNY * C::NNX);
+  float* const s_red = s_un + C::UNION + 2 * C::NNY * C::NNX + 2 * C::NG * 64;
+
+  const WgIdx wg = xcd_order();
+  const int pair = wg.z;
+  if (slot_off(g.mask, pair)) return;
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), band = wave >> 1;
+  const int half = wave < 2 * C::NG ? wave & 1 : 2;   // 2: no shifts
+  const int a0 = wg.y * TH, b0 = wg.x * TW;
+  const int y0 = a0 * STEP - STEP / 2, x0 = b0 * STEP - STEP / 2;   // A tile origin
+  const int yb = y0 - R, xb = x0 - R;                              // B' tile origin
+  const uint8_t* Ai = g.A + (int64_t)pair * g.stride;
+  const uint8_t* Bi = g.B + (int64_t)pair * g.stride;
+  const int np = g.nx * g.ny, rowbytes = g.W * ES;
+  const float* Pn = g.pred ? g.pred + (int64_t)pair * 2 * np : nullptr;
+  const bool cell_ok = lane < C::NC;
+  const int ci = cell_ok ? lane / C::CW : 0, cj = cell_ok ? lane - (lane / C::CW) * C::CW : 0;
+
+  // predictor nodes covering the B' tile: every wave reads all of them and
+  // takes their range itself (no barrier before the raw box is requested)
+  const float cen = 0.5f * (float)(STEP - 1);
+  const int nlo_y = max(0, (int)floorf(((float)yb - cen) / STEP));
+  const int nlo_x = max(0, (int)floorf(((float)xb - cen) / STEP));
+  constexpr int NNODE = C::NNY * C::NNX, NL = (NNODE + 63) / 64;
+  float nu[NL], nv[NL];
+  if (Pn) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int idx = min(lane + 64 * i, NNODE - 1);
+      const int r = idx / C::NNX, q = idx - (idx / C::NNX) * C::NNX;
+      const int o = __umul24(min(nlo_y + r, g.ny - 1), g.nx) + min(nlo_x + q, g.nx - 1);
+      nu[i] = Pn[(unsigned)o];
+      nv[i] = Pn[(unsigned)(np + o)];
+    }
+  }
+  // a frame whose bytes fit 31 bits (pitch below 2^24) is addressed by 32-bit
+  // offsets from its base, with 24-bit products
+  const bool off32 = g.pitch < (1 << 24) && g.pitch * (int64_t)g.H <= 0x7fffffff;
+  const unsigned pitch32 = (unsigned)g.pitch;
+  // rows band, band + 3, .. of this lane's A cell as packed pixels (zero
+  // outside the image), by the second wave of the band
+  constexpr int NAR = kCentral ? 1 : STEP / C::NG;
+  static_assert(kCentral || STEP % C::NG == 0, "cell rows split evenly over the bands");
+  uint32_t aw[NAR][NWR];
+  if (!kCentral && half == 1) {
+    const int xa0 = (x0 + cj * STEP) * ES;
+    const bool inside = off32 && y0 >= 0 && y0 + C::AH <= g.H && x0 >= 0 && (x0 + C::AW) * ES <= rowbytes;
+#pragma unroll
+    for (int i = 0; i < NAR; ++i) {
+      const int y = y0 + ci * STEP + band + C::NG * i;
+      if (inside) {
+        const unsigned o = __umul24((unsigned)y, pitch32) + (unsigned)xa0;
+#pragma unroll
+        for (int k = 0; k < NWR; ++k)
+          aw[i][k] = cell_ok ? *reinterpret_cast<const uint32_t*>(Ai + (size_t)(o + 4 * k)) : 0u;
+      } else {
+        const uint32_t ok = (cell_ok && (unsigned)y < (unsigned)g.H) ? 0xffffffffu : 0u;
+        const uint8_t* row = Ai + (int64_t)min(max(y, 0), g.H - 1) * g.pitch;
+#pragma unroll
+        for (int k = 0; k < NWR; ++k) aw[i][k] = masked_word(row, rowbytes, xa0 + 4 * k) & ok;
+      }
+    }
+  }
+  // range of the (scaled) nodes as integer floors: see k_correct_bands
+  float lu = 0.0f, hu = 0.0f, lv = 0.0f, hv = 0.0f;
+  bool nodes_ok = true;
+  if (Pn) {
+    lu = hu = nu[0];
+    lv = hv = nv[0];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      lu = fminf(lu, nu[i]);
+      hu = fmaxf(hu, nu[i]);
+      lv = fminf(lv, nv[i]);
+      hv = fmaxf(hv, nv[i]);
+      nodes_ok = nodes_ok && fabsf(nu[i]) < 100.0f && fabsf(nv[i]) < 100.0f;   // false for NaN
+    }
+    if (t < 64) {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        const int idx = lane + 64 * i;
+        if (idx < NNODE) {
+          const int r = idx / C::NNX, q = idx - (idx / C::NNX) * C::NNX;
+          s_node[0][r][q] = nu[i];
+          s_node[1][r][q] = nv[i];
+        }
+      }
+    }
+  }
+  uint32_t* sraw = reinterpret_cast<uint32_t*>(s_un);
+  int* s_rb = reinterpret_cast<int*>(s_un + C::RAW_WORDS);   // per B' row: base node, fraction
+  float* s_rf = s_un + C::RAW_WORDS + C::BH;
+  int* s_cb = reinterpret_cast<int*>(s_un + C::RAW_WORDS + 2 * C::BH);   // per B' column
+  float* s_cf = s_un + C::RAW_WORDS + 2 * C::BH + C::BW;
+  // stage the raw source box of a frame for its tile rows x cols at (ty, tx)
+  // deformed by sgn * u, when it fits
+  struct Box { int ix0, iy0, nwords; bool staged; };
+  auto stage = [&](const uint8_t* img, int ty, int tx, int rows, int cols, float sgn) __attribute__((always_inline)) {
+    int flu = 0, fhu = 0, flv = 0, fhv = 0;
+    if (Pn) {
+      const float xl = sgn < 0.0f ? sgn * hu : sgn * lu, xh = sgn < 0.0f ? sgn * lu : sgn * hu;
+      const float yl = sgn < 0.0f ? sgn * hv : sgn * lv, yh = sgn < 0.0f ? sgn * lv : sgn * hv;
+      // encoded so that a max serves every bound: 127 - floor(lo) and
+      // floor(hi) + 128, two 16-bit fields per word, each reduced on its own;
+      // 255 marks the tile
+      const uint32_t el_u = nodes_ok ? 127 - (int)floorf(xl) : 255, eh_u = nodes_ok ? (int)floorf(xh) + 128 : 255;
+      const uint32_t el_v = nodes_ok ? 127 - (int)floorf(yl) : 255, eh_v = nodes_ok ? (int)floorf(yh) + 128 : 255;
+      const uint32_t ru = wave_max_pk16((el_u << 16) | eh_u), rv = wave_max_pk16((el_v << 16) | eh_v);
+      flu = 127 - (int)(ru >> 16);
+      fhu = (int)(ru & 0xffffu) - 128;
+      flv = 127 - (int)(rv >> 16);
+      fhv = (int)(rv & 0xffffu) - 128;
+    }
+    Box b;
+    b.ix0 = tx + flu - 1;
+    b.iy0 = ty + flv - 1;
+    const int ix1 = tx + cols - 1 + fhu + 2, iy1 = ty + rows - 1 + fhv + 2;
+    const int xw0 = (b.ix0 * ES) >> 2;
+    b.nwords = ((ix1 * ES + ES - 1) >> 2) - xw0 + 1;
+    const int nrows = iy1 - b.iy0 + 1;
+    b.staged = fhu - flu < 64 && fhv - flv < 64 && b.nwords <= NT && b.nwords * nrows <= C::RAW_WORDS;
+    if (b.staged) {
+      // thread -> (word column, first row); U reads in flight per thread
+      const int rstep = NT / b.nwords;
+      const int r0 = t / b.nwords, w = t - r0 * b.nwords;
+      constexpr int U = STEP == 8 ? 5 : 14;
+      const bool inside = off32 && b.iy0 >= 0 && b.iy0 + nrows <= g.H && xw0 >= 0 && 4 * (xw0 + b.nwords) <= rowbytes;
+      if (r0 < rstep) {
+        // slots past the box take its last row again (the same word is
+        // written twice with the same value), so the stores need no branch
+        for (int rb = r0; rb < nrows; rb += U * rstep) {
+          uint32_t val[U];
+          if (inside) {
+            const unsigned col = 4u * (unsigned)(xw0 + w);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              const unsigned y = (unsigned)(b.iy0 + min(rb + u * rstep, nrows - 1));
+              val[u] = *reinterpret_cast<const uint32_t*>(img + (size_t)(__umul24(y, pitch32) + col));
+            }
+          } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              const int y = b.iy0 + min(rb + u * rstep, nrows - 1);
+              const uint32_t ok = (unsigned)y < (unsigned)g.H ? 0xffffffffu : 0u;
+              val[u] = masked_word(img + (int64_t)min(max(y, 0), g.H - 1) * g.pitch, rowbytes, 4 * (xw0 + w)) & ok;
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) sraw[min(rb + u * rstep, nrows - 1) * b.nwords + w] = val[u];
+        }
+      }
+    }
+    return b;
+  };
+  // deform the tile (ROWS x COLS at (ty, tx), tables from row / column TO)
+  // by sgn * u, minus K, into dst (pitch DP); returns the thread's sum
+  auto deform = [&](const uint8_t* img, const Box& b, int ty, int tx, auto rows_c, auto cols_c, auto to_c, auto dp_c,
+                    float sgn, float K, float* dst) __attribute__((always_inline)) {
+    constexpr int ROWS = decltype(rows_c)::value, COLS = decltype(cols_c)::value, TO = decltype(to_c)::value;
+    constexpr int DP = decltype(dp_c)::value;
+    float sum = 0.0f;
+    if (b.staged) {
+      // groups of four pixels of one row, two groups per pass, so that one
+      // group's LDS round trips overlap the other's arithmetic; coordinates
+      // relative to the box, where the floor is a truncation and every corner
+      // lies inside (see k_correct_bands)
+      constexpr int BQ = COLS / 4;
+      const int rowb = 4 * b.nwords, xadd = b.ix0 * ES - 4 * ((b.ix0 * ES) >> 2);
+      const uint8_t* rawx = reinterpret_cast<const uint8_t*>(sraw) + xadd;
+      auto rawv = [&](const uint8_t* p) -> float { return (float)*reinterpret_cast<const T*>(p); };
+      auto group = [&](int idx) __attribute__((always_inline)) {
+        const int r = idx / BQ, q = 4 * (idx - (idx / BQ) * BQ);
+        float uu[4] = {0.0f, 0.0f, 0.0f, 0.0f}, vv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (Pn) {
+          // (no group straddles a node column: step and r are multiples of 4)
+          const int rb = s_rb[TO + r];
+          const float fy = s_rf[TO + r];
+          const int cb0 = s_cb[TO + q];
+          const float u0 = s_node[0][rb][cb0] + fy * (s_node[0][rb + 1][cb0] - s_node[0][rb][cb0]);
+          const float u1 = s_node[0][rb][cb0 + 1] + fy * (s_node[0][rb + 1][cb0 + 1] - s_node[0][rb][cb0 + 1]);
+          const float v0 = s_node[1][rb][cb0] + fy * (s_node[1][rb + 1][cb0] - s_node[1][rb][cb0]);
+          const float v1 = s_node[1][rb][cb0 + 1] + fy * (s_node[1][rb + 1][cb0 + 1] - s_node[1][rb][cb0 + 1]);
+          const float du = u1 - u0, dv = v1 - v0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float fx = s_cf[TO + q + e];
+            uu[e] = u0 + fx * du;
+            vv[e] = v0 + fx * dv;
+            if constexpr (kCentral) {
+              uu[e] *= sgn;
+              vv[e] *= sgn;
+            }
+          }
+        }
+        const float yr = (float)(ty + r - b.iy0), xq = (float)(tx + q - b.ix0);
+        float out[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float qx = (xq + (float)e) + uu[e], qy = yr + vv[e];
+          const float fx = __builtin_amdgcn_fractf(qx), fy = __builtin_amdgcn_fractf(qy);
+          const unsigned ix = (unsigned)(int)qx, iy = (unsigned)(int)qy;
+          const uint8_t* p0 = rawx + (__umul24(iy, (unsigned)rowb) + ix * ES);
+          const float p00 = rawv(p0), p01 = rawv(p0 + ES), p10 = rawv(p0 + rowb), p11 = rawv(p0 + rowb + ES);
+          const float top = p00 + fx * (p01 - p00), bot = p10 + fx * (p11 - p10);
+          out[e] = (top + fy * (bot - top)) - K;
+        }
+        if constexpr (kCentral) sum += (out[0] + out[1]) + (out[2] + out[3]);
+        *reinterpret_cast<float4*>(dst + r * DP + q) = make_float4(out[0], out[1], out[2], out[3]);
+      };
+      constexpr int NGR = ROWS * BQ;
+      int idx = t;
+      for (; idx + NT < NGR; idx += 2 * NT) {
+        group(idx);
+        group(idx + NT);
+      }
+      if (idx < NGR) group(idx);
+    } else {
+      for (int idx = t; idx < ROWS * COLS; idx += NT) {
+        const int r = idx / COLS, q = idx - (idx / COLS) * COLS;
+        const int y = ty + r, x = tx + q;
+        float v;
+        if (Pn) {
+          const int rb = s_rb[TO + r], cb = s_cb[TO + q];
+          const float fy = s_rf[TO + r], fx = s_cf[TO + q];
+          const float u = (1.0f - fy) * ((1.0f - fx) * s_node[0][rb][cb] + fx * s_node[0][rb][cb + 1]) +
+                          fy * ((1.0f - fx) * s_node[0][rb + 1][cb] + fx * s_node[0][rb + 1][cb + 1]);
+          const float w = (1.0f - fy) * ((1.0f - fx) * s_node[1][rb][cb] + fx * s_node[1][rb][cb + 1]) +
+                          fy * ((1.0f - fx) * s_node[1][rb + 1][cb] + fx * s_node[1][rb + 1][cb + 1]);
+          v = bilin<T>(img, g.pitch, g.W, g.H, kCentral ? x + sgn * u : x + u, kCentral ? y + sgn * w : y + w);
+        } else {
+          v = pixf<T>(img, g.pitch, g.W, g.H, y, x);
+        }
+        sum += v;
+        dst[r * DP + q] = v - K;
+      }
+    }
+    return sum;
+  };
+  // interpolation tables of the B' tile (the same arithmetic as interp_u)
+  for (int i = t; i < C::BH + C::BW; i += NT) {
+    const bool row = i < C::BH;
+    const int p = row ? yb + i : xb + (i - C::BH);
+    const int n = row ? g.ny : g.nx;
+    float tt = fminf(fmaxf(((float)p - cen) / (float)STEP, 0.0f), (float)(n - 1));
+    int bb = min((int)tt, max(n - 2, 0));
+    float ff = tt - (float)bb;
+    if (row) { s_rb[i] = bb - nlo_y; s_rf[i] = ff; }
+    else { s_cb[i - C::BH] = bb - nlo_x; s_cf[i - C::BH] = ff; }
+  }
+  auto unpack = [](const uint32_t (&wd)[NWR], float (&an)[STEP]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int x = 0; x < STEP; ++x) {
+      const uint32_t v = wd[(x * ES) >> 2];
+      an[x] = (float)(ES == 1 ? (v >> (8 * (x & 3))) & 0xffu : (v >> (16 * (x & 1))) & 0xffffu);
+    }
+  };
+  // pixel row py of this lane's A cell as floats
+  uint32_t* const s_cell = reinterpret_cast<uint32_t*>(s_un + C::XW) + lane * C::CP;
+  auto arow = [&](int py, float (&an)[STEP]) __attribute__((always_inline)) {
+    if constexpr (kCentral) {
+      const float* p = sA + (ci * STEP + py) * C::AP + cj * STEP;
+#pragma unroll
+      for (int x = 0; x < STEP; ++x) an[x] = p[x];
+    } else {
+      uint32_t wd[NWR];
+#pragma unroll
+      for (int k = 0; k < NWR; ++k) wd[k] = s_cell[py * NWR + k];
+      unpack(wd, an);
+    }
+  };
+  // K, the rounded mean of the A tile, and the cells' sums of A - K and its
+  // square (rows dealt to the bands, by the second wave of each)
+  float K;
+  auto cell_sums = [&]() __attribute__((always_inline)) {
+    float s1 = 0.0f, s2 = 0.0f;
+    auto add = [&](const float (&an)[STEP]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int x = 0; x < STEP; ++x) {
+        const float d = an[x] - K;
+        s1 += d;
+        s2 += d * d;
+      }
+    };
+    float an[STEP];
+    if constexpr (kCentral) {
+#pragma unroll
+      for (int py = 0; py < STEP; ++py) {
+        if (py % C::NG != band) continue;
+        arow(py, an);
+        add(an);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NAR; ++i) {
+        unpack(aw[i], an);
+        add(an);
+      }
+    }
+    s_asum[0][band][lane] = s1;
+    s_asum[1][band][lane] = s2;
+  };
+  if constexpr (kCentral) {
+    const Box ba = stage(Ai, y0, x0, C::AH, C::AW, -0.5f);
+    __syncthreads();
+    float part = deform(Ai, ba, y0, x0, Int<C::AH>(), Int<C::AW>(), Int<R>(), Int<C::AP>(), -0.5f, 0.0f, sA);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
+    if (lane == 0) s_red[t >> 6] = part;
+    __syncthreads();
+    K = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) K += s_red[i];
+    K = rintf(K / (float)(C::AH * C::AW));
+  } else {
+    // (integers: the waves' sums meet exactly)
+    int isum = 0;
+    if (half == 1) {
+#pragma unroll
+      for (int i = 0; i < NAR; ++i)
+#pragma unroll
+        for (int k = 0; k < NWR; ++k) {
+          if constexpr (ES == 1) isum = (int)__builtin_amdgcn_sad_u8(aw[i][k], 0u, (uint32_t)isum);
+          else isum = (int)__builtin_amdgcn_sad_u16(aw[i][k], 0u, (uint32_t)isum);
+        }
+    }
+    isum = wave_sum(isum);
+    if (lane == 0) s_red[t >> 6] = __int_as_float(isum);
+  }
+  const Box bb = stage(Bi, yb, xb, C::BH, C::BW, kCentral ? 0.5f : 1.0f);
+  __syncthreads();
+  if constexpr (!kCentral) {
+    int isum = 0;
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) isum += __float_as_int(s_red[i]);
+    K = (float)((isum + C::AH * C::AW / 2) / (C::AH * C::AW));   // (isum >= 0)
+  }
+  if (half == 1) cell_sums();
+  deform(Bi, bb, yb, xb, Int<C::BH>(), Int<C::BW>(), Int<0>(), Int<C::BP>(), kCentral ? 0.5f : 1.0f, K, sB);
+  if constexpr (!kCentral) {
+    // the packed cells take the raw box's place
+    __syncthreads();
+    if (half == 1) {
+#pragma unroll
+      for (int i = 0; i < NAR; ++i)
+#pragma unroll
+        for (int k = 0; k < NWR; ++k) s_cell[(band + C::NG * i) * NWR + k] = aw[i][k];
+    }
+  }
+  __syncthreads();
+
+  // ---- this lane's cell against the wave's shifts
+  constexpr int BRW = STEP + 2 * R;   // B' columns one cell row needs
+  const float* bbase = sB + (ci * STEP + band * SYG) * C::BP + cj * STEP;
+  // window sums: (cell + right-hand neighbour) by DPP wave_shl:1, then + the
+  // same pair one cell row down (lane + CW) by a lane permute.  Only lanes of
+  // a window's top-left cell keep meaningful sums.
+  auto quad = [&](float x) {
+    const float h = x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130, 0xF, 0xF, false));
+    return h + __int_as_float(__builtin_amdgcn_ds_bpermute((lane + C::CW) << 2, __float_as_int(h)));
+  };
+  // P = sum A (B' - K) of the shift columns J0 .. J0 + NJ - 1: the B' rows of
+  // the band streamed once each; B' row rb meets A row rb - k for shift row
+  // k, so the last SYG A rows are kept
+  auto products = [&](auto j0_c, auto nj_c, float (&P)[SYG][C::H1]) __attribute__((always_inline)) {
+    constexpr int J0 = decltype(j0_c)::value, NJ = decltype(nj_c)::value, NB = STEP + NJ - 1;
+#pragma unroll
+    for (int k = 0; k < SYG; ++k)
+#pragma unroll
+      for (int j = 0; j < C::H1; ++j) P[k][j] = 0.0f;
+    float ar[SYG][STEP];
+#pragma unroll
+    for (int rb = 0; rb < STEP + SYG - 1; ++rb) {
+      float brow[NB];
+#pragma unroll
+      for (int x = 0; x < NB; ++x) brow[x] = bbase[rb * C::BP + J0 + x];
+      if (rb < STEP) arow(rb, ar[rb % SYG]);
+#pragma unroll
+      for (int k = 0; k < SYG; ++k) {
+        const int py = rb - k;
+        if (py >= 0 && py < STEP) {
+          const float* ap = ar[py % SYG];
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            float s = P[k][j];
+#pragma unroll
+            for (int x = 0; x < STEP; ++x) s += ap[x] * brow[x + j];
+            P[k][j] = s;
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);   // (one row's reads ahead would not fit the registers)
+    }
+  };
+  // box sums of B' - K (kSq: of its square) over STEP columns for every
+  // shift: column sums of the band's first STEP rows, slid down for the
+  // other rows
+  auto boxes = [&](auto sq_c, float (&o)[SYG][NSY]) __attribute__((always_inline)) {
+    constexpr bool kSq = decltype(sq_c)::value;
+    float c[BRW];
+#pragma unroll
+    for (int x = 0; x < BRW; ++x) c[x] = 0.0f;
+#pragma unroll
+    for (int rb = 0; rb < STEP; ++rb) {
+#pragma unroll
+      for (int x = 0; x < BRW; ++x) {
+        const float b = bbase[rb * C::BP + x];
+        if constexpr (kSq) c[x] += b * b;
+        else c[x] += b;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < SYG; ++k) {
+      if (k > 0) {
+        const float* rin = bbase + (STEP + k - 1) * C::BP;
+        const float* rout = bbase + (k - 1) * C::BP;
+#pragma unroll
+        for (int x = 0; x < BRW; ++x) {
+          const float vi = rin[x], vo = rout[x];
+          if constexpr (kSq) c[x] += vi * vi - vo * vo;
+          else c[x] += vi - vo;
+        }
+      }
+      float s = 0.0f;
+#pragma unroll
+      for (int x = 0; x < STEP; ++x) s += c[x];
+      o[k][0] = s;
+#pragma unroll
+      for (int j = 1; j < NSY; ++j) {
+        s += c[j + STEP - 1] - c[j - 1];
+        o[k][j] = s;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < SYG; ++k)
+#pragma unroll
+      for (int j = 0; j < NSY; ++j) o[k][j] = quad(o[k][j]);
+  };
+  const bool wact = cell_ok && ci < TH && cj < TW;
+  const int w = ci * TW + cj;
+  float sa = 0.0f, saa = 0.0f;
+#pragma unroll
+  for (int q = 0; q < C::NG; ++q) {
+    sa += s_asum[0][q][lane];
+    saa += s_asum[1][q][lane];
+  }
+  sa = quad(sa);
+  saa = quad(saa);
+  float P[SYG][C::H1], SQ[SYG][NSY];   // SQ: S in the band's first wave, Q in its second
+  // what the other wave needs: [band][shift row][column][window]
+  float* const sx = s_un + band * (C::NWIN * SYG * NSY) + w;
+  if (half == 0) {
+    products(Int<0>(), Int<C::H0>(), P);
+    boxes(std::false_type(), SQ);
+  } else if (half == 1) {
+    products(Int<C::H0>(), Int<C::H1>(), P);
+    boxes(std::true_type(), SQ);
+  }
+  if (half < 2) {
+#pragma unroll
+    for (int k = 0; k < SYG; ++k)
+#pragma unroll
+      for (int j = 0; j < C::H1; ++j) P[k][j] = quad(P[k][j]);
+  }
+  // (the raw box and the tables were last read before the barrier above)
+  if (wact && half < 2) {
+#pragma unroll
+    for (int k = 0; k < SYG; ++k)
+#pragma unroll
+      for (int j = 0; j < NSY; ++j)
+        if ((j >= C::H0) == (half == 0)) sx[(k * NSY + j) * C::NWIN] = SQ[k][j];
+  }
+  __syncthreads();
+  // ---- Pearson coefficient per shift, the wave's peak by the tie key
+  float* const rhoW = s_un + C::XW;                    // [window][shift]
+  float* const s_best = rhoW + C::NWIN * C::NS;        // [wave][window]
+  int* const s_pk = reinterpret_cast<int*>(s_best + 2 * C::NG * C::NWIN);
+  auto peak = [&](auto j0_c, auto nj_c) __attribute__((always_inline)) {
+    constexpr int J0 = decltype(j0_c)::value, NJ = decltype(nj_c)::value;
+    constexpr float kInvN = 1.0f / (float)(4 * STEP * STEP);
+    const float mA = sa * kInvN;
+    const float varA = saa - sa * mA;
+    const float meanA = K + mA;
+    const bool flatA = !(varA > kFlatRel * saa);
+    float rv[SYG][NJ];
+    bool allflat = true;   // every used shift of the wave is flat
+#pragma unroll
+    for (int k = 0; k < SYG; ++k)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const float other = wact ? sx[(k * NSY + J0 + j) * C::NWIN] : 1.0f;
+        const float S = J0 == 0 ? SQ[k][J0 + j] : other, Q = J0 == 0 ? other : SQ[k][J0 + j];
+        const float num = P[k][j] - meanA * S;
+        const float varB = Q - S * S * kInvN;
+        const bool flat = flatA || !(varB > kFlatRel * Q);
+        // (varA varB > 0 unless flat; the flat value replaces the quotient)
+        const float r = num * __builtin_amdgcn_rsqf(varA * varB);
+        rv[k][j] = flat ? 0.0f : r;
+        allflat = allflat && flat;
+      }
+    float best = -2.0f;
+    int bkey = 1 << 20;
+#pragma unroll
+    for (int k = 0; k < SYG; ++k)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) best = fmaxf(best, rv[k][j]);
+#pragma unroll
+    for (int k = 0; k < SYG; ++k)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        bkey = rv[k][j] == best ? min(bkey, tie_key(band * SYG + k - R, J0 + j - R)) : bkey;
+    if (wact) {
+      float* d = rhoW + w * C::NS + band * SYG * NSY + J0;
+#pragma unroll
+      for (int k = 0; k < SYG; ++k)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) d[k * NSY + j] = rv[k][j];
+      s_best[wave * C::NWIN + w] = best;
+      s_pk[wave * C::NWIN + w] = (bkey << 1) | (allflat ? 1 : 0);
+    }
+  };
+  if (half == 0) peak(Int<0>(), Int<C::H0>());
+  else if (half == 1) peak(Int<C::H0>(), Int<C::H1>());
+  __syncthreads();
+  // ---- peak over the waves, fit, composition with the predictor's window
+  // mean; the windows are dealt to the waves
+  constexpr int WPW = C::NWIN / (2 * C::NG);
+  static_assert(WPW * 2 * C::NG == C::NWIN, "windows split evenly over the waves");
+  const int wt = wave * WPW + lane;
+  if (lane < WPW && half < 2) {
+    const int wi = wt / TW, wj = wt - (wt / TW) * TW;
+    const int a = a0 + wi, b = b0 + wj;
+    if (a < g.ny && b < g.nx) {
+      float best = -2.0f;
+      int bkey = 1 << 20;
+      bool allflat = true;
+#pragma unroll
+      for (int q = 0; q < 2 * C::NG; ++q) {
+        const float bq = s_best[q * C::NWIN + wt];
+        const int pk = s_pk[q * C::NWIN + wt];
+        allflat = allflat && (pk & 1);
+        if (better(bq, pk >> 1, best, bkey)) {
+          best = bq;
+          bkey = pk >> 1;
+        }
+      }
+      const int sx_ = (bkey & 63) - 32, sy_ = ((bkey >> 6) & 63) - 32;
+      const float* rr = rhoW + wt * C::NS;
+      auto rhof = [&](int y, int x) { return rr[(y + R) * NSY + x + R]; };
+      auto node = [&](int c, int y, int x) { return s_node[c][y - nlo_y][x - nlo_x]; };
+      float pu = 0.0f, pv = 0.0f;
+      if (Pn) window_mean_half_overlap(a, b, g.nx, g.ny, node, pu, pv);
+      finish_vector(g, pair, a, b, sy_, sx_, allflat, pu, pv, rhof);
     }
   }
 }
@@ -2169,14 +2764,23 @@ hipError_t launch_rows(const CorrArgs& g, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <typename T, int STEP, bool kCentral>
+hipError_t launch_halves(const CorrArgs& g, int n, hipStream_t s) {
+  constexpr int TW = 8, TH = 6;
+  constexpr size_t lds = sizeof(float) * HalvesCfg<T, STEP, TW, TH, kCentral>::LDS_WORDS;
+  dim3 grid((g.nx + TW - 1) / TW, (g.ny + TH - 1) / TH, n);
+  hipLaunchKernelGGL((k_correct_halves<T, STEP, TW, TH, kCentral>), grid, dim3(512), lds, s, g);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_tiled_t(const CorrArgs& g, int n, hipStream_t s) {
   if (!g.central && g.step == 8 && g.R == 4) return launch_bands<T, 8, 4, 3, 8, 6>(g, n, s);
   if (!g.central && g.step == 8 && g.R == 1) return launch_bands<T, 8, 1, 1, 8, 6>(g, n, s);
   if constexpr (sizeof(T) == 2) {   // (u8 cells of 12 px are not whole words at half a cell)
-    if (!g.central && g.step == 12 && g.R == 4) return launch_bands<T, 12, 4, 3, 8, 6>(g, n, s);
+    if (!g.central && g.step == 12 && g.R == 4) return launch_halves<T, 12, false>(g, n, s);
   }
-  if (g.step == 8 && g.R == 4) return launch_tiled<T, 8, 4, 3, 8, 8, 256>(g, n, s);
+  if (g.step == 8 && g.R == 4) return launch_halves<T, 8, true>(g, n, s);
   if (g.step == 8 && g.R == 1) return launch_tiled<T, 8, 1, 1, 8, 8, 256>(g, n, s);
   if (g.step == 12 && g.R == 4) return launch_tiled<T, 12, 4, 3, 5, 5, 128>(g, n, s);
   if (g.step == 12 && g.R == 1) return launch_tiled<T, 12, 1, 1, 5, 5, 128>(g, n, s);
