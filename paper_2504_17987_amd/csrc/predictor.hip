@@ -1444,6 +1444,319 @@ __global__ __launch_bounds__(256) void k_pred_out(const int32_t* d, int64_t dstr
   }
 }
 
+// ---------------------------------------------------------------------------
+// SAD block search with cell-shared sums for 32x32 blocks at step 16.  A
+// block is four 16x16 cells that it shares with its neighbours.  A thread
+// takes one cell and one row of shifts (or every PARTS-th row of the cell's
+// pixels for it), streams A and B rows from LDS and keeps the SADs of all
+// shift columns: u8 four per quad SAD in 16-bit fields (a cell is at most
+// 256 x 255), u16 by v_sad_u16 on realigned words.  The cells' sums meet in
+// LDS; a thread per (node, shift row) adds four cells and takes its least
+// key, a thread per node the least of those.  Few nodes make a search of
+// these blocks latency-bound: 512 nodes of 4 u8 pairs at R 6 took 20 us with
+// a thread per node, candidate column and two candidate rows (k_sad), now
+// 7 us; the finer level's 2,048 x 4 nodes at R 2 27 us, now 9 us.
+// ---------------------------------------------------------------------------
+// The SADs of one cell row against the B row words rw (realigned to shift
+// column 0): accumulators of G columns
+template <typename T, int G>
+struct CellSad {
+  static constexpr int ES = (int)sizeof(T), CWD = 4 * ES;          // words of a cell row
+  static constexpr int NGRP = (G + 3) / 4, REM = G - 4 * (NGRP - 1);
+  static constexpr bool TAIL = REM <= 2;                           // last u8 group by full-rate v_sad_u8
+  static constexpr int NQ = TAIL ? NGRP - 1 : NGRP;
+  static constexpr int RW = ES == 1 ? CWD + NGRP : CWD + (G + 1) / 2;   // realigned words needed
+  static constexpr int NACC = ES == 1 && NQ > 0 ? NQ : 1, NSUM = ES == 1 ? 2 : G;
+  typedef uint32_t U32x2 __attribute__((ext_vector_type(2)));
+  typedef unsigned long long Acc[NACC];
+  typedef uint32_t Sum[NSUM];
+  static __device__ __forceinline__ void clear(Acc& acc, Sum& sum) {
+#pragma unroll
+    for (int m = 0; m < NACC; ++m) acc[m] = 0ull;
+#pragma unroll
+    for (int c = 0; c < NSUM; ++c) sum[c] = 0u;
+  }
+  // one row: al(i) is the i-th realigned B word.  (Called per word: kept in
+  // an array, the pairs of the quad SADs become unaligned 8-byte reads of it,
+  // and the array stays in memory.)
+  template <typename F>
+  static __device__ __forceinline__ void row(const uint32_t (&a)[CWD], F al, Acc& acc, Sum& sum) {
+    if constexpr (ES == 1) {
+#pragma unroll
+      for (int i = 0; i < CWD; ++i) {
+#pragma unroll
+        for (int m = 0; m < NQ; ++m) {
+          const U32x2 src = {al(i + m), al(i + m + 1)};
+          acc[m] = __builtin_amdgcn_qsad_pk_u16_u8(__builtin_bit_cast(unsigned long long, src), a[i], acc[m]);
+        }
+        if constexpr (TAIL) {
+          sum[0] = __builtin_amdgcn_sad_u8(a[i], al(i + NQ), sum[0]);
+          if constexpr (REM == 2)
+            sum[1] = __builtin_amdgcn_sad_u8(a[i], __builtin_amdgcn_alignbyte(al(i + NQ + 1), al(i + NQ), 1), sum[1]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < G; ++c)
+#pragma unroll
+        for (int i = 0; i < CWD; ++i)
+          sum[c] = __builtin_amdgcn_sad_u16(
+              a[i], (c & 1) ? __builtin_amdgcn_alignbyte(al(c / 2 + i + 1), al(c / 2 + i), 2) : al(c / 2 + i), sum[c]);
+    }
+  }
+  // f(shift column, SAD) for every column
+  template <typename F>
+  static __device__ __forceinline__ void each(const Acc& acc, const Sum& sum, F f) {
+    if constexpr (ES == 1) {
+#pragma unroll
+      for (int m = 0; m < NQ; ++m)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (4 * m + k < G) f(4 * m + k, (uint32_t)(acc[m] >> (16 * k)) & 0xffffu);
+      if constexpr (TAIL) {
+#pragma unroll
+        for (int k = 0; k < REM; ++k) f(4 * NQ + k, sum[k]);
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < G; ++c) f(c, sum[c]);
+    }
+  }
+};
+
+// Coarsest level (every node searches the same shifts): a workgroup is a
+// tile of TN x TN nodes.
+template <typename T, int R, int TN, int PARTS>
+struct Sad32Cfg {
+  static constexpr int ES = (int)sizeof(T), G = 2 * R + 1, CN = TN + 1, NC = CN * CN;
+  static constexpr int NI = NC * G * PARTS, NT = (NI + 63) / 64 * 64;
+  static constexpr int AH = 16 * CN, BH = AH + 2 * R;
+  static constexpr int AP = 4 * ES * CN;                          // words per A row
+  static constexpr int SH = ((-8 - R) * ES) & 3;                  // B rows start that far into their first word
+  static constexpr int BP = 4 * ES * (CN - 1) + CellSad<T, G>::RW + 2;   // words per B row
+};
+
+template <typename T, int R, int TN, int PARTS>
+__global__ __launch_bounds__((Sad32Cfg<T, R, TN, PARTS>::NT)) void k_sad_coarse32(SadArgs g) {
+  using C = Sad32Cfg<T, R, TN, PARTS>;
+  constexpr int G = C::G, NT = C::NT;
+  using S = CellSad<T, G>;
+  __shared__ __align__(16) uint32_t sA[C::AH * C::AP];
+  __shared__ __align__(16) uint32_t sB[C::BH * C::BP];
+  __shared__ uint32_t sX[C::NC * G * G];          // [shift row][cell][shift column]
+  __shared__ unsigned long long s_key[TN * TN * G];
+  const int pair = blockIdx.z, t = threadIdx.x;
+  if (slot_off(g.mask, pair)) return;
+  const int a0 = blockIdx.y * TN, b0 = blockIdx.x * TN;
+  const int y0 = 16 * a0 - 8, x0 = 16 * b0 - 8;
+  const uint8_t* Ab = g.A + (int64_t)pair * g.stride;
+  const uint8_t* Bb = g.B + (int64_t)pair * g.stride;
+  // rows and words of the tile, clamped into the padded level (a tile may
+  // overhang the grid; what it then reads twice is not used)
+  const int ymax = g.H + g.margin - 1, wmax = (int)((g.pitch - (int64_t)g.margin * C::ES) >> 2) - 1;
+  {
+    // (every read first, then the LDS stores)
+    constexpr int NA = (C::AH * C::AP + NT - 1) / NT, NB = (C::BH * C::BP + NT - 1) / NT;
+    uint32_t va[NA], vb[NB];
+#pragma unroll
+    for (int u = 0; u < NA; ++u) {
+      const int i = min(t + u * NT, C::AH * C::AP - 1), r = i / C::AP, w = i - (i / C::AP) * C::AP;
+      va[u] = *reinterpret_cast<const uint32_t*>(Ab + (int64_t)min(y0 + r, ymax) * g.pitch +
+                                                 4 * min(((x0 * C::ES) >> 2) + w, wmax));
+    }
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      const int i = min(t + u * NT, C::BH * C::BP - 1), r = i / C::BP, w = i - (i / C::BP) * C::BP;
+      vb[u] = *reinterpret_cast<const uint32_t*>(Bb + (int64_t)min(y0 - R + r, ymax) * g.pitch +
+                                                 4 * min((((x0 - R) * C::ES) >> 2) + w, wmax));
+    }
+#pragma unroll
+    for (int u = 0; u < NA; ++u)
+      if (t + u * NT < C::AH * C::AP) sA[t + u * NT] = va[u];
+#pragma unroll
+    for (int u = 0; u < NB; ++u)
+      if (t + u * NT < C::BH * C::BP) sB[t + u * NT] = vb[u];
+  }
+  __syncthreads();
+  const int q = t / PARTS, part = t - q * PARTS, dyi = q % G, cell = q / G;
+  if (t < C::NI) {
+    const int ci = cell / C::CN, cj = cell - (cell / C::CN) * C::CN;
+    typename S::Acc acc;
+    typename S::Sum sum;
+    S::clear(acc, sum);
+    const uint32_t* pa = sA + ci * 16 * C::AP + cj * S::CWD;
+    const uint32_t* pb = sB + (ci * 16 + dyi) * C::BP + cj * S::CWD;
+#pragma unroll 2
+    for (int k = 0; k < 16 / PARTS; ++k) {
+      const int py = part + PARTS * k;
+      uint32_t a[S::CWD], w[S::RW + 1];
+#pragma unroll
+      for (int i = 0; i < S::CWD; ++i) a[i] = pa[py * C::AP + i];
+#pragma unroll
+      for (int i = 0; i <= S::RW; ++i) w[i] = pb[py * C::BP + i];
+      S::row(a, [&](int i) __attribute__((always_inline)) {
+        return C::SH ? __builtin_amdgcn_alignbyte(w[i + 1], w[i], C::SH) : w[i];
+      }, acc, sum);
+    }
+    uint32_t* o = sX + (dyi * C::NC + cell) * G;
+    S::each(acc, sum, [&](int c, uint32_t v) __attribute__((always_inline)) {
+      if constexpr (PARTS == 2) v += (uint32_t)PIV_DPP_I((int)v, 0xB1, 0xF, 0);   // the neighbouring lane's rows
+      if (PARTS == 1 || part == 0) o[c] = v;
+    });
+  }
+  __syncthreads();
+  for (int i = t; i < TN * TN * G; i += NT) {
+    const int node = i / G, k = i - node * G, na = node / TN, nb = node - na * TN;
+    const uint32_t* p = sX + (k * C::NC + na * C::CN + nb) * G;
+    unsigned long long best = ~0ull;
+#pragma unroll
+    for (int c = 0; c < G; ++c) {
+      const unsigned long long key =
+          sad_key((p[c] + p[G + c]) + (p[C::CN * G + c] + p[(C::CN + 1) * G + c]), k - R, c - R);
+      best = key < best ? key : best;
+    }
+    s_key[i] = best;
+  }
+  __syncthreads();
+  if (t < TN * TN) {
+    const int a = a0 + t / TN, b = b0 + t % TN;
+    if (a < g.ny && b < g.nx) {
+      unsigned long long m = s_key[t * G];
+#pragma unroll
+      for (int k = 1; k < G; ++k) m = s_key[t * G + k] < m ? s_key[t * G + k] : m;
+      int32_t* out = g.out + (int64_t)pair * g.ostride;
+      out[a * g.nx + b] = (int)(m & 0xff) - 128;
+      out[g.nx * g.ny + a * g.nx + b] = (int)((m >> 8) & 0xff) - 128;
+    }
+  }
+}
+
+// Finer levels: a wave per parent, whose four children search the same
+// shifts and share a 3x3 group of cells.  Lane = (cell, shift row).
+template <typename T, int R>
+__global__ __launch_bounds__(256) void k_sad_fine32(SadArgs g) {
+  constexpr int ES = (int)sizeof(T), G = 2 * R + 1, NL = 9 * G;
+  static_assert(NL <= 64, "a lane per cell and shift row");
+  using S = CellSad<T, G>;
+  constexpr int AP = 12 * ES, BP = 8 * ES + S::RW + 1, AH = 48, BH = AH + 2 * R;   // words per row, rows
+  __shared__ __align__(16) uint32_t sA[4][AH * AP];
+  __shared__ __align__(16) uint32_t sB[4][BH * BP];
+  __shared__ uint32_t sX[4][NL * G];            // [cell][shift row][shift column]
+  __shared__ unsigned long long s_key[4][4 * G];
+  const WgIdx wg = xcd_order();
+  const int pair = wg.z;
+  if (slot_off(g.mask, pair)) return;
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int pnx = (g.nx + 1) / 2, pny = (g.ny + 1) / 2;
+  const int tile = min(wg.x * 4 + wv, pnx * pny - 1);   // (waves past the last parent repeat it)
+  const int pa = tile / pnx, pb = tile - (tile / pnx) * pnx;
+  const int y0 = 32 * pa - 8, x0 = 32 * pb - 8;
+  int cx_, cy_;
+  const uint8_t* Ab = g.A + (int64_t)pair * g.stride;
+  const uint8_t* Bb = g.B + (int64_t)pair * g.stride;
+  // rows and words, clamped into the padded level (the group of an odd last
+  // parent overhangs the grid; what it then reads twice is not used)
+  const int ymax = g.H + g.margin - 1, wmax = (int)((g.pitch - (int64_t)g.margin * ES) >> 2) - 1;
+  uint32_t* const tA = sA[wv];
+  uint32_t* const tB = sB[wv];
+  {
+    // (every read first, then the LDS stores; those of A do not wait for the
+    // parent's centre)
+    constexpr int NA = (AH * AP + 63) / 64, NB = (BH * BP + 63) / 64;
+    uint32_t va[NA], vb[NB];
+#pragma unroll
+    for (int u = 0; u < NA; ++u) {
+      const int i = min(lane + u * 64, AH * AP - 1), r = i / AP, w = i - (i / AP) * AP;
+      va[u] = *reinterpret_cast<const uint32_t*>(Ab + (int64_t)min(y0 + r, ymax) * g.pitch +
+                                                 4 * min(((x0 * ES) >> 2) + w, wmax));
+    }
+    int cx, cy;
+    parent_centre(g, g.parent + (int64_t)pair * g.pstride, min(pa, g.pny - 1), min(pb, g.pnx - 1), cx, cy);
+    cx_ = __builtin_amdgcn_readfirstlane(cx);
+    cy_ = __builtin_amdgcn_readfirstlane(cy);
+    const int xs = (x0 + cx_ - R) * ES;
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      const int i = min(lane + u * 64, BH * BP - 1), r = i / BP, w = i - (i / BP) * BP;
+      vb[u] = *reinterpret_cast<const uint32_t*>(Bb + (int64_t)min(y0 + cy_ - R + r, ymax) * g.pitch +
+                                                 4 * min((xs >> 2) + w, wmax));
+    }
+#pragma unroll
+    for (int u = 0; u < NA; ++u)
+      if (lane + u * 64 < AH * AP) tA[lane + u * 64] = va[u];
+#pragma unroll
+    for (int u = 0; u < NB; ++u)
+      if (lane + u * 64 < BH * BP) tB[lane + u * 64] = vb[u];
+  }
+  const int cx = cx_, cy = cy_, sh = ((x0 + cx - R) * ES) & 3;
+  __syncthreads();
+  if (lane < NL) {
+    const int cell = lane / G, dyi = lane - cell * G, u = cell / 3, v = cell - 3 * (cell / 3);
+    typename S::Acc acc;
+    typename S::Sum sum;
+    S::clear(acc, sum);
+    const uint32_t* qa = tA + u * 16 * AP + v * S::CWD;
+    const uint32_t* qb = tB + (u * 16 + dyi) * BP + v * S::CWD;
+#pragma unroll 4
+    for (int py = 0; py < 16; ++py) {
+      uint32_t a[S::CWD], w[S::RW + 1];
+#pragma unroll
+      for (int i = 0; i < S::CWD; ++i) a[i] = qa[py * AP + i];
+#pragma unroll
+      for (int i = 0; i <= S::RW; ++i) w[i] = qb[py * BP + i];
+      S::row(a, [&](int i) __attribute__((always_inline)) { return __builtin_amdgcn_alignbyte(w[i + 1], w[i], sh); },
+             acc, sum);
+    }
+    S::each(acc, sum, [&](int c, uint32_t v) __attribute__((always_inline)) { sX[wv][lane * G + c] = v; });
+  }
+  __syncthreads();
+  const int child = lane / G, k = lane - child * G;   // child = 2 u + v
+  if (lane < 4 * G) {
+    const uint32_t* p = sX[wv] + (((child >> 1) * 3 + (child & 1)) * G + k) * G;
+    unsigned long long best = ~0ull;
+#pragma unroll
+    for (int c = 0; c < G; ++c) {
+      const unsigned long long key =
+          sad_key((p[c] + p[G * G + c]) + (p[3 * G * G + c] + p[4 * G * G + c]), cy - R + k, cx - R + c);
+      best = key < best ? key : best;
+    }
+    s_key[wv][lane] = best;
+  }
+  __syncthreads();
+  if (lane < 4) {
+    const int a = 2 * pa + (lane >> 1), b = 2 * pb + (lane & 1);
+    if (a < g.ny && b < g.nx) {
+      unsigned long long m = s_key[wv][lane * G];
+#pragma unroll
+      for (int q = 1; q < G; ++q) m = s_key[wv][lane * G + q] < m ? s_key[wv][lane * G + q] : m;
+      int32_t* out = g.out + (int64_t)pair * g.ostride;
+      out[a * g.nx + b] = (int)(m & 0xff) - 128;
+      out[g.nx * g.ny + a * g.nx + b] = (int)((m >> 8) & 0xff) - 128;
+    }
+  }
+}
+
+template <typename T, int R, int TN, int PARTS>
+hipError_t launch_coarse32(const SadArgs& g, int n, hipStream_t s) {
+  dim3 grid((g.nx + TN - 1) / TN, (g.ny + TN - 1) / TN, n);
+  hipLaunchKernelGGL((k_sad_coarse32<T, R, TN, PARTS>), grid, dim3(Sad32Cfg<T, R, TN, PARTS>::NT), 0, s, g);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_coarse32_r(const SadArgs& g, int n, hipStream_t s) {
+  // tiles of 2 x 2 nodes spread a small level over the chip, 4 x 4 share more
+  // cells: equal at 4,096 nodes (piv_predict, u8, R 6 / R 8: 16.7 / 19.7 and
+  // 16.2 / 17.1 us; at 16,384 nodes 37 / 51 and 33 / 38 us)
+  const bool big = (int64_t)g.nx * g.ny * n >= 4096;
+  switch (g.R) {
+#define PIV_C32(R_) case R_: return big ? launch_coarse32<T, R_, 4, 1>(g, n, s) : launch_coarse32<T, R_, 2, 2>(g, n, s);
+    PIV_C32(3) PIV_C32(4) PIV_C32(5) PIV_C32(6) PIV_C32(7) PIV_C32(8)
+#undef PIV_C32
+    default: return hipErrorInvalidValue;
+  }
+}
+
 template <int ES, int NW>
 hipError_t sad_dispatch_k(int G, dim3 grid, size_t lds, hipStream_t s, const SadArgs& g) {
   if (G <= 5) hipLaunchKernelGGL((k_sad<ES, NW, 5>), grid, dim3(256), lds, s, g);
@@ -1681,6 +1994,22 @@ hipError_t launch_sad_level(const Plan& P, int l, const void* A, const void* B, 
     }
 #undef PIV_SAD8
     return hipGetLastError();
+  }
+  // 32x32 blocks at step 16: cell-shared sums
+  if (P.p.step == 16 && P.block == 32) {
+    if (!g.parent && g.R >= 3 && g.R <= 8)
+      return P.es == 1 ? launch_coarse32_r<uint8_t>(g, n, s) : launch_coarse32_r<uint16_t>(g, n, s);
+    if (g.parent && g.R >= 1 && g.R <= 2) {
+      const dim3 grid((((v.nx + 1) / 2) * ((v.ny + 1) / 2) + 3) / 4, 1, n);
+      if (P.es == 1) {
+        if (g.R == 2) hipLaunchKernelGGL((k_sad_fine32<uint8_t, 2>), grid, dim3(256), 0, s, g);
+        else hipLaunchKernelGGL((k_sad_fine32<uint8_t, 1>), grid, dim3(256), 0, s, g);
+      } else {
+        if (g.R == 2) hipLaunchKernelGGL((k_sad_fine32<uint16_t, 2>), grid, dim3(256), 0, s, g);
+        else hipLaunchKernelGGL((k_sad_fine32<uint16_t, 1>), grid, dim3(256), 0, s, g);
+      }
+      return hipGetLastError();
+    }
   }
   // nodes per workgroup: G lanes each, A blocks within 64 KiB of LDS
   const int npw = min(256 / G, 65536 / (P.block * NW * 4));
