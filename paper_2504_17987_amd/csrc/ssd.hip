@@ -227,191 +227,238 @@ __global__ __launch_bounds__(256) void k_ssd_backward(SsdArgs a, int TN) {
 }
 
 // ---------------------------------------------------------------------------
-// Tiled forms for win = 2 step (the plans' geometry).  A workgroup owns a
-// TN x TN tile (of windows forward, of nodes backward).  The nodes covering
-// the tile's pixel region are cached in LDS with per-row / per-column
-// interpolation tables; samples of A and B are read from global memory (L1
-// serves the bilinear neighbours), which keeps LDS small and occupancy high
-// enough to hide the read latency.
+// Tiled forms for 16 px windows on an 8 px step (the plans' geometry).  A
+// workgroup owns an 8 x 8 tile (of windows forward, of nodes backward); its
+// pixel region is nine strips of eight rows by nine cells of eight columns,
+// strip k = 0 .. ny holding the rows 8 k - 4 .. 8 k + 3: the rows of a strip
+// share their base node row, the windows that hold them and, with the nearest
+// node, only two owners.  A thread takes a strip's eight pixels of one
+// column, so the lanes of a wave read neighbouring columns: three cache lines
+// a gather, where groups of four pixels of a row per lane touch nine (the
+// forward then took 69 us, 64 pairs of 512 x 512, instead of 38).
 // ---------------------------------------------------------------------------
-template <int STEP, int TN>
-struct SsdTile {
-  static constexpr int H2 = STEP / 2;                 // (win - step) / 2
-  static constexpr int RW = (TN + 1) * STEP;          // max region side (px)
-  static constexpr int NNC = RW / STEP + 3;           // cached node rows / columns
-  static constexpr int NG = RW / STEP + 2;            // cached window rows / columns
+constexpr int kStep = 8;                 // the step, and the pixels of a strip or cell
+constexpr int kTile = 8;                 // windows or nodes a side
+constexpr int kStrips = kTile + 1;       // strips and cells a side
+constexpr int kCols = kStrips * kStep;   // region columns
+constexpr int kNodes = kTile + 2;        // cached node rows and columns, from ta - 1 and tb - 1 on
+
+// What a strip's rows (or a cell's columns) share: the cache index of the base
+// node and the fractions towards the next node, f0 + e df for row e.  The
+// node coordinate (y - 3.5) / 8 is clamped to the grid, so the first strip
+// rests on node 0 and the last on node n - 1.
+struct SsdCell {
+  int base;
+  float f0, df;
 };
 
-// The cached nodes and tables of a region [ylo, ylo+RH) x [xlo, xlo+RW_).
-template <int STEP, int TN>
-struct SsdShared {
-  using C = SsdTile<STEP, TN>;
-  float node[2][C::NNC][C::NNC];
-  int rb[C::RW], cb[C::RW];       // base node (cache index)
-  float rf[C::RW], cf[C::RW];     // fraction towards base + 1
-};
+__device__ __forceinline__ SsdCell ssd_cell_of(int k, int n, int t0) {
+  SsdCell c;
+  c.base = min(max(k - 1, 0), max(n - 2, 0)) - (t0 - 1);
+  c.df = k > 0 && k < n ? 0.125f : 0.0f;
+  c.f0 = k <= 0 || n <= 1 ? 0.0f : k < n ? 0.0625f : 1.0f;
+  return c;
+}
 
-// Loads the node cache and the interpolation tables of the region rows and
-// columns (base node as a cache index, fraction towards base + 1).
-// Returns (the same in every thread) whether the tile is interior: every
-// pixel of the region lies in the frames and so does every bilinear sample
-// with its right and lower neighbours, with a pixel to spare.  The samples
-// of region pixel x lie at x + u with u between the cached nodes' extremes
-// (the interpolation stays within them), so the nodes decide; a NaN node
-// makes the tile not interior.
-template <int STEP, int TN>
-__device__ __forceinline__ bool ssd_prepare(const SsdArgs& a, const float* U, int ylo, int xlo, int RH, int RWc,
-                                            SsdShared<STEP, TN>& sh, int& nly, int& nlx) {
-  using C = SsdTile<STEP, TN>;
+// fraction of row e (kInside: no strip of the tile is clamped)
+template <bool kInside>
+__device__ __forceinline__ float ssd_fraction(const SsdCell& c, int e) {
+  return kInside ? 0.0625f + 0.125f * (float)e : c.f0 + (float)e * c.df;
+}
+
+// Deals the region's columns: item(st, j) for strip st, column j.  A wave
+// takes the first 64 columns of a strip, whose rows' values it then holds in
+// scalar registers; the last cell's eight columns of all strips come last.
+template <class Item>
+__device__ __forceinline__ void ssd_deal(int t, Item item) {
+  const int lane = t & 63;
+  int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  for (; w < kStrips; w += 4) item(w, lane);
+  const int st = (w - kStrips) * 8 + (lane >> 3);
+  if (st < kStrips) item(st, 64 + (lane & 7));
+}
+
+// Loads the tile's node cache.  Returns (the same in every thread) whether
+// the tile is interior: no strip or cell is clamped, every pixel of the
+// region lies in the frames and so does every bilinear sample with its right
+// and lower neighbours, with a pixel to spare.  The samples of region pixel x
+// lie at x + u with u between the cached nodes' extremes (the interpolation
+// stays within them), so the nodes decide; a NaN node makes the tile not
+// interior.
+__device__ __forceinline__ bool ssd_nodes(const SsdArgs& a, const float* U, int ta, int tb,
+                                          float (&node)[2][kNodes][kNodes]) {
   const int t = threadIdx.x;
-  const float cen = 0.5f * (float)(STEP - 1);
-  nly = max(0, (int)floorf(((float)ylo - cen) / STEP));
-  nlx = max(0, (int)floorf(((float)xlo - cen) / STEP));
   const int np = a.nx * a.ny;
-  const int xhi = xlo + RWc - 1, yhi = ylo + RH - 1;
-  bool inside = xlo >= 0 && ylo >= 0 && xhi <= a.W - 1 && yhi <= a.H - 1;
-  for (int i = t; i < C::NNC * C::NNC; i += 256) {
-    const int r = i / C::NNC, q = i - (i / C::NNC) * C::NNC;
-    const int ny_ = min(nly + r, a.ny - 1), nx_ = min(nlx + q, a.nx - 1);
-    const float u = U[ny_ * a.nx + nx_], v = U[np + ny_ * a.nx + nx_];
-    sh.node[0][r][q] = u;
-    sh.node[1][r][q] = v;
+  const int tae = min(ta + kTile, a.ny) - 1, tbe = min(tb + kTile, a.nx) - 1;
+  const int ylo = ta * kStep - kStep / 2, yhi = (tae + 1) * kStep + kStep / 2 - 1;
+  const int xlo = tb * kStep - kStep / 2, xhi = (tbe + 1) * kStep + kStep / 2 - 1;
+  bool inside = ta > 0 && tb > 0 && tae < a.ny - 1 && tbe < a.nx - 1 && yhi < a.H && xhi < a.W;
+  if (t < kNodes * kNodes) {
+    const int r = t / kNodes, q = t - (t / kNodes) * kNodes;
+    const int i = min(max(ta - 1 + r, 0), a.ny - 1) * a.nx + min(max(tb - 1 + q, 0), a.nx - 1);
+    const float u = U[i], v = U[np + i];
+    node[0][r][q] = u;
+    node[1][r][q] = v;
     inside = inside && (float)xlo + u >= 1.0f && (float)xhi + u <= (float)(a.W - 3) && (float)ylo + v >= 1.0f &&
              (float)yhi + v <= (float)(a.H - 3);
-  }
-  for (int i = t; i < RH + RWc; i += 256) {
-    const bool row = i < RH;
-    const int pp = row ? ylo + i : xlo + (i - RH);
-    const int n = row ? a.ny : a.nx;
-    int bb;
-    float ff;
-    node_coord((float)pp, n, STEP, bb, ff);
-    if (row) { sh.rb[i] = bb - nly; sh.rf[i] = ff; }
-    else { sh.cb[i - RH] = bb - nlx; sh.cf[i - RH] = ff; }
   }
   return __syncthreads_and(inside ? 1 : 0) != 0;
 }
 
-// bilinear sample bs = B(x + u, y + v) at the pixel (x, y), given as floats
-// xf, yf, and its floor-cell gradient: with top/bottom the row
-// interpolations of the cell, bs = top + ey (bottom - top), dbs/dy =
-// bottom - top and dbs/dx the row differences interpolated in y.  kInside:
-// the tile is interior (every read in the frames), so the reads need no
-// bounds tests and take 32-bit byte offsets from the frame base (a frame
-// holds fewer than 2^30 pixels).
+// Four-byte reads of a frame at byte offsets from its base, 32 bits (a frame
+// holds fewer than 2^30 pixels, a side fewer than 2^15).  kInside: plain
+// reads, both columns of a cell's row in one.  Else through a buffer
+// descriptor of the frame: a pixel beyond the frame gets the offset kBeyond,
+// which the hardware answers with zero, without a branch (a frame ends
+// before it).
+struct __attribute__((aligned(4))) SsdTwo {
+  float x, y;
+};
+constexpr uint32_t kBeyond = 0xfffffffcu;
+
+struct SsdFrame {
+  const char* base;
+  __amdgpu_buffer_rsrc_t rsrc;
+};
+
+__device__ __forceinline__ SsdFrame ssd_frame(const SsdArgs& a, const float* I) {
+  SsdFrame f;
+  f.base = reinterpret_cast<const char*>(I);
+  f.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(I), 0, (int)(4u * (uint32_t)a.W * (uint32_t)a.H),
+                                             0x00020000);
+  return f;
+}
+
+__device__ __forceinline__ float ssd_beyond(const SsdFrame& f, bool in, uint32_t o) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(f.rsrc, (int)(in ? o : kBeyond), 0, 0));
+}
+
+// the bilinear cell of B at (ix, iy)
 template <bool kInside>
-__device__ __forceinline__ void ssd_sample(const SsdArgs& a, const float* B, float xf, float yf, float u, float v,
-                                           float& bs, float& gx, float& gy) {
-  const float qx = xf + u, qy = yf + v;
-  const float x0 = floorf(qx), y0 = floorf(qy);
-  const float ex = qx - x0, ey = qy - y0;
-  const int ix = (int)x0, iy = (int)y0;
-  float p00, p01, p10, p11;
+__device__ __forceinline__ void ssd_corners(const SsdArgs& a, const SsdFrame& f, int ix, int iy, float& p00, float& p01,
+                                            float& p10, float& p11) {
+  const uint32_t ow = 4u * (uint32_t)a.W;
   if constexpr (kInside) {
-    const char* Bb = reinterpret_cast<const char*>(B);
-    const uint32_t o = 4u * (uint32_t)(iy * a.W + ix), ow = 4u * (uint32_t)a.W;
-    p00 = *reinterpret_cast<const float*>(Bb + o);
-    p01 = *reinterpret_cast<const float*>(Bb + o + 4u);
-    p10 = *reinterpret_cast<const float*>(Bb + (o + ow));
-    p11 = *reinterpret_cast<const float*>(Bb + (o + ow) + 4u);
+    const uint32_t o = (uint32_t)__umul24((uint32_t)iy, ow) + 4u * (uint32_t)ix;
+    const SsdTwo top = *reinterpret_cast<const SsdTwo*>(f.base + o);
+    const SsdTwo bot = *reinterpret_cast<const SsdTwo*>(f.base + (o + ow));
+    p00 = top.x;
+    p01 = top.y;
+    p10 = bot.x;
+    p11 = bot.y;
   } else {
-    p00 = ldA(B, a.W, a.H, iy, ix);
-    p01 = ldA(B, a.W, a.H, iy, ix + 1);
-    p10 = ldA(B, a.W, a.H, iy + 1, ix);
-    p11 = ldA(B, a.W, a.H, iy + 1, ix + 1);
+    const bool x0 = (uint32_t)ix < (uint32_t)a.W, x1 = (uint32_t)ix + 1u < (uint32_t)a.W;
+    const bool y0 = (uint32_t)iy < (uint32_t)a.H, y1 = (uint32_t)iy + 1u < (uint32_t)a.H;
+    const uint32_t o = (uint32_t)__mul24(iy, (int)ow) + 4u * (uint32_t)ix;   // (right where it is used)
+    p00 = ssd_beyond(f, x0 && y0, o);
+    p01 = ssd_beyond(f, x1 && y0, o + 4u);
+    p10 = ssd_beyond(f, x0 && y1, o + ow);
+    p11 = ssd_beyond(f, x1 && y1, o + ow + 4u);
   }
-  const float d0 = p01 - p00, d1 = p11 - p10;
-  const float top = p00 + ex * d0, bot = p10 + ex * d1;
-  gy = bot - top;
-  bs = top + ey * gy;
-  gx = d0 + ey * (d1 - d0);
 }
 
 // A at the pixel (x, y) (zero outside the frame)
 template <bool kInside>
-__device__ __forceinline__ float ssd_a(const SsdArgs& a, const float* A, int x, int y) {
-  if constexpr (kInside)
-    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(A) + 4u * (uint32_t)(y * a.W + x));
-  else
-    return ldA(A, a.W, a.H, y, x);
+__device__ __forceinline__ float ssd_a(const SsdArgs& a, const SsdFrame& f, int x, int y) {
+  const uint32_t o = (uint32_t)__mul24(y, 4 * a.W) + 4u * (uint32_t)x;
+  if constexpr (kInside) return *reinterpret_cast<const float*>(f.base + o);
+  else return ssd_beyond(f, (uint32_t)x < (uint32_t)a.W && (uint32_t)y < (uint32_t)a.H, o);
 }
 
-// residual r = B'(p) - A(p) and the sample's gradient at the pixel (x, y)
-// for a given displacement (u, v) of that pixel
-template <bool kInside>
-__device__ __forceinline__ void ssd_residual_uv(const SsdArgs& a, const float* A, const float* B, int x, int y,
-                                                float xf, float yf, float u, float v, float& r, float& gx,
-                                                float& gy) {
-  float bs;
-  ssd_sample<kInside>(a, B, xf, yf, u, v, bs, gx, gy);
-  r = bs - ssd_a<kInside>(a, A, x, y);
+// One column of a strip: for each of its eight pixels, with (u, v) =
+// disp(e), use(e, r, gx, gy) gets the residual r = B(x + u, y + v) - A(x, y)
+// and the sample's floor-cell gradient: with top/bottom the row
+// interpolations of the cell, bs = top + ey (bottom - top), dbs/dy =
+// bottom - top and dbs/dx the row differences interpolated in y.  Four
+// pixels' reads are in flight together.
+template <bool kInside, class Disp, class Use>
+__device__ __forceinline__ void ssd_column(const SsdArgs& a, const SsdFrame& A, const SsdFrame& B, int x, int y0, Disp disp,
+                                           Use use) {
+  const float xf = (float)x, yf = (float)y0;
+#pragma unroll
+  for (int h = 0; h < kStep; h += 4) {
+    float ex[4], ey[4], av[4], p00[4], p01[4], p10[4], p11[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float u, v;
+      disp(h + e, u, v);
+      const float qx = xf + u, qy = (yf + (float)(h + e)) + v;
+      const float x0 = floorf(qx), y0f = floorf(qy);
+      ex[e] = qx - x0;
+      ey[e] = qy - y0f;
+      ssd_corners<kInside>(a, B, (int)x0, (int)y0f, p00[e], p01[e], p10[e], p11[e]);
+      av[e] = ssd_a<kInside>(a, A, x, y0 + h + e);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float d0 = p01[e] - p00[e], d1 = p11[e] - p10[e];
+      const float top = p00[e] + ex[e] * d0, bot = p10[e] + ex[e] * d1;
+      const float gy = bot - top;
+      use(h + e, (top + ey[e] * gy) - av[e], d0 + ey[e] * (d1 - d0), gy);
+    }
+  }
 }
 
-// the same at region pixel (i, j), its displacement interpolated from the
-// cached nodes
-template <bool kInside, int STEP, int TN>
-__device__ __forceinline__ void ssd_residual(const SsdArgs& a, const float* A, const float* B,
-                                             const SsdShared<STEP, TN>& sh, int ylo, int xlo, int i, int j,
-                                             float& r, float& gx, float& gy) {
-  const int rb = sh.rb[i], cb = sh.cb[j];
-  const float fy = sh.rf[i], fx = sh.cf[j];
-  const float u = (1.0f - fy) * ((1.0f - fx) * sh.node[0][rb][cb] + fx * sh.node[0][rb][cb + 1]) +
-                  fy * ((1.0f - fx) * sh.node[0][rb + 1][cb] + fx * sh.node[0][rb + 1][cb + 1]);
-  const float v = (1.0f - fy) * ((1.0f - fx) * sh.node[1][rb][cb] + fx * sh.node[1][rb][cb + 1]) +
-                  fy * ((1.0f - fx) * sh.node[1][rb + 1][cb] + fx * sh.node[1][rb + 1][cb + 1]);
-  ssd_residual_uv<kInside>(a, A, B, xlo + j, ylo + i, (float)(xlo + j), (float)(ylo + i), u, v, r, gx, gy);
-}
-
-// Forward, TN x TN windows per workgroup: squared residuals of the tile's
-// pixel region in LDS, then 4 threads per window sum its block.
-template <int STEP, int TN>
-__global__ __launch_bounds__(256) void k_ssd_forward_t(SsdArgs a) {
-  using C = SsdTile<STEP, TN>;
-  constexpr int WIN = 2 * STEP, RWF = (TN - 1) * STEP + WIN;
-  static_assert(RWF <= C::RW, "forward region");
-  __shared__ SsdShared<STEP, TN> sh;
-  __shared__ float s_r2[RWF * RWF];
+// Forward: the squared residuals of every column of a strip are summed in its
+// thread, then 4 threads per window add a quarter of its 2 strips x 16
+// columns each.  Bound by the address rate of the vector caches (23 million
+// accesses, some 16 a gather, or 38 us at one a cycle and CU; 46 VALU
+// operations a pixel are 25 us): 64 pairs of 512 x 512 38 us (57 us with a
+// thread per pixel, which weighed its four nodes by itself and read the
+// cell's corners one by one).
+__global__ __launch_bounds__(256, 6) void k_ssd_forward_t(SsdArgs a) {
+  __shared__ float node[2][kNodes][kNodes];
+  __shared__ __attribute__((aligned(16))) float s_r2[kStrips][kCols];
   const WgIdx wg = xcd_order();
   const int pair = wg.z;
   if (slot_off(a.mask, pair)) return;
   const int t = threadIdx.x;
   const int np = a.nx * a.ny;
   const int64_t img = (int64_t)a.W * a.H;
-  const float* A = a.A + pair * img;
-  const float* B = a.B + pair * img;
+  const SsdFrame A = ssd_frame(a, a.A + pair * img), B = ssd_frame(a, a.B + pair * img);
   const float* U = a.U + (int64_t)pair * 2 * np;
-  const int ta = wg.y * TN, tb = wg.x * TN;
-  const int ylo = ta * STEP - C::H2, xlo = tb * STEP - C::H2;
-  int nly, nlx;
-  const bool interior = ssd_prepare<STEP, TN>(a, U, ylo, xlo, RWF, RWF, sh, nly, nlx);
+  const int ta = wg.y * kTile, tb = wg.x * kTile;
+  const bool interior = ssd_nodes(a, U, ta, tb, node);
   auto squares = [&](auto inside) {
     constexpr bool kIn = decltype(inside)::value;
-    for (int idx = t; idx < RWF * RWF; idx += 256) {
-      const int i = idx / RWF, j = idx - (idx / RWF) * RWF;
-      float r, gx, gy;
-      ssd_residual<kIn, STEP, TN>(a, A, B, sh, ylo, xlo, i, j, r, gx, gy);
-      s_r2[idx] = r * r;
-    }
+    ssd_deal(t, [&](int st, int j) __attribute__((always_inline)) {
+      if (ta + st > a.ny || tb + j / kStep > a.nx) return;   // no window of the tile holds it
+      const SsdCell row = ssd_cell_of(ta + st, a.ny, ta), col = ssd_cell_of(tb + j / kStep, a.nx, tb);
+      const float fx = ssd_fraction<kIn>(col, j & (kStep - 1));
+      const int rb = kIn ? st : row.base, cb = kIn ? j / kStep : col.base;
+      const float uT = node[0][rb][cb] + fx * (node[0][rb][cb + 1] - node[0][rb][cb]);
+      const float uB = node[0][rb + 1][cb] + fx * (node[0][rb + 1][cb + 1] - node[0][rb + 1][cb]);
+      const float vT = node[1][rb][cb] + fx * (node[1][rb][cb + 1] - node[1][rb][cb]);
+      const float vB = node[1][rb + 1][cb] + fx * (node[1][rb + 1][cb + 1] - node[1][rb + 1][cb]);
+      const float du = uB - uT, dv = vB - vT;
+      float s = 0.0f;
+      ssd_column<kIn>(
+          a, A, B, tb * kStep - kStep / 2 + j, (ta + st) * kStep - kStep / 2,
+          [&](int e, float& u, float& v) {
+            const float fy = ssd_fraction<kIn>(row, e);
+            u = uT + fy * du;
+            v = vT + fy * dv;
+          },
+          [&](int, float r, float, float) { s += r * r; });
+      s_r2[st][j] = s;
+    });
   };
   if (interior) squares(std::true_type{});
   else squares(std::false_type{});
   __syncthreads();
   const int w = t >> 2, p = t & 3;
-  const int wi = w / TN, wj = w - (w / TN) * TN;
+  const int wi = w / kTile, wj = w - (w / kTile) * kTile;
+  const int aa = ta + wi, bb = tb + wj;
+  const bool act = aa < a.ny && bb < a.nx;
   float s = 0.0f;
-  if (w < TN * TN) {
-    for (int i = p; i < WIN; i += 4) {
-      const float* row = s_r2 + (wi * STEP + i) * RWF + wj * STEP;
-#pragma unroll
-      for (int j = 0; j < WIN; ++j) s += row[j];
-    }
+  if (act) {
+    const float4* q = reinterpret_cast<const float4*>(&s_r2[wi + (p >> 1)][(wj + (p & 1)) * kStep]);
+    const float4 lo = q[0], hi = q[1];
+    s = ((lo.x + lo.y) + (lo.z + lo.w)) + ((hi.x + hi.y) + (hi.z + hi.w));
   }
   s += __shfl_xor(s, 1);
   s += __shfl_xor(s, 2);
-  if (w < TN * TN && p == 0) {
-    const int aa = ta + wi, bb = tb + wj;
-    if (aa < a.ny && bb < a.nx) a.loss[(int64_t)pair * a.lstride + aa * a.nx + bb] = s;
-  }
+  if (act && p == 0) a.loss[(int64_t)pair * a.lstride + aa * a.nx + bb] = s;
 }
 
 // Sum over a 256-thread workgroup in a fixed order (every thread gets it).
@@ -428,211 +475,139 @@ __device__ __forceinline__ float tile_sum(float x, float* red) {
   return red[0];
 }
 
-// Backward, TN x TN nodes per workgroup.  Every pixel of the nodes' support
-// region contributes to the two node columns and two node rows of its
+// Backward, 8 x 8 nodes per workgroup.  Every pixel of the nodes' support
+// region contributes to the two node rows and two node columns of its
 // bilinear cell (weights 1-f and f, squared for the diagonal), so the
-// adjoint separates: pass 1 sums each (pixel row, STEP-pixel chunk) into
-// left/right column partials of the four terms 2 m r gx, 2 m r gy,
-// 2 m gx^2, 2 m gy^2; pass 2 sums a node's partials over its rows with the
-// row weights.  Chunks of STEP pixels starting at the region edge share one
-// base node column (the region starts on a cell boundary), and m (the sum
-// of the upstream gradients of the windows holding the pixel) is constant
-// along a chunk.
-template <int STEP, int TN, bool kPart>
-__global__ __launch_bounds__(256) void k_ssd_backward_t(SsdArgs a) {
-  using C = SsdTile<STEP, TN>;
-  constexpr int NCH = C::RW / STEP;                    // chunks per region row
-  static_assert(STEP % 4 == 0, "chunks of whole groups of four pixels");
-  __shared__ SsdShared<STEP, TN> sh;
-  __shared__ float s_part[C::RW][NCH][8];              // [row][chunk][term*2 + side]
-  __shared__ float s_g[C::NG][C::NG];                  // upstream window gradients
-  __shared__ int s_chb[NCH];                           // base node column of a chunk
-  __shared__ int s_rfirst[C::NNC], s_rlast[C::NNC];    // region rows based on each cached node row
-  __shared__ float s_red[256];                         // fixed-order tile sums
-  __shared__ uint8_t s_ownr[C::RW], s_ownc[C::RW];     // region rows / columns whose nearest node is the tile's
-  __shared__ float4 s_cw[C::RW];                       // per region column: wr (the fraction), wl, wr^2, wl^2
+// adjoint separates: pass 1 sums each column of a strip into upper/lower node
+// row partials of the four terms 2 m r gx, 2 m r gy, 2 m gx^2, 2 m gy^2 (m,
+// the sum of the upstream gradients of the windows holding the pixel, is
+// constant along it); pass 2 sums a node's partials over its columns with
+// the column weights.  The displacement is interpolated down the two node
+// columns and then across, the order that decides in which cell a sample at a
+// cell's edge falls.  Bound by VALU issue, some 50 operations a pixel and 80
+// at the frames' border: 64 pairs of 512 x 512 50 us (99 us with a thread per
+// eight pixels of a row, whose gathers touched a cache line per lane and whose
+// node sums read every row's partials).
+constexpr int kPartPlane = kCols + 1;               // odd: the terms' planes on different banks,
+constexpr int kPartStrip = 8 * kPartPlane + 1;      // and the strips of a wave's node rows too
+
+template <bool kPart>
+__global__ __launch_bounds__(256, 6) void k_ssd_backward_t(SsdArgs a) {
+  __shared__ float node[2][kNodes][kNodes];
+  __shared__ float s_part[kStrips * kPartStrip];       // [strip][term*2 + side][column]
+  __shared__ float s_g[kNodes][kNodes];                // upstream gradients of the windows from ta - 1 and tb - 1 on
+  __shared__ float s_red[kPart ? 256 : 1];             // fixed-order tile sums
   const WgIdx wg = xcd_order();
   const int pair = wg.z;
   if (slot_off(a.mask, pair)) return;
   const int t = threadIdx.x;
   const int np = a.nx * a.ny;
   const int64_t img = (int64_t)a.W * a.H;
-  const float* A = a.A + pair * img;
-  const float* B = a.B + pair * img;
+  const SsdFrame A = ssd_frame(a, a.A + pair * img), B = ssd_frame(a, a.B + pair * img);
   const float* U = a.U + (int64_t)pair * 2 * np;
   const float* G = a.g ? a.g + (int64_t)pair * np : nullptr;
-  const int ta = wg.y * TN, tb = wg.x * TN;
-  constexpr int h = C::H2;
-  const int lo_all = -h, hi_x = a.nx * STEP + h - 1, hi_y = a.ny * STEP + h - 1;
-  const int ylo = ta == 0 ? lo_all : (ta - 1) * STEP + STEP / 2;
-  const int xlo = tb == 0 ? lo_all : (tb - 1) * STEP + STEP / 2;
-  const int tae = min(ta + TN, a.ny) - 1, tbe = min(tb + TN, a.nx) - 1;
-  const int yhi = tae == a.ny - 1 ? hi_y : (tae + 1) * STEP + (STEP - 1) / 2;
-  const int xhi = tbe == a.nx - 1 ? hi_x : (tbe + 1) * STEP + (STEP - 1) / 2;
-  const int RH = yhi - ylo + 1, RWc = xhi - xlo + 1;
-  // upstream gradients of the windows that can hold a region pixel:
-  // window rows i with i STEP - h <= y <= i STEP - h + 2 STEP - 1
-  const int gi0 = max((ylo + h) / STEP - 1, 0), gj0 = max((xlo + h) / STEP - 1, 0);
-  for (int i = t; i < C::NG * C::NG; i += 256) {
-    const int r = i / C::NG, q = i - (i / C::NG) * C::NG;
-    const int gi = gi0 + r, gj = gj0 + q;
-    s_g[r][q] = (gi < a.ny && gj < a.nx) ? (G ? G[gi * a.nx + gj] : 1.0f) : 0.0f;
+  const int ta = wg.y * kTile, tb = wg.x * kTile;
+  const int tae = min(ta + kTile, a.ny) - 1, tbe = min(tb + kTile, a.nx) - 1;
+  if (t < kNodes * kNodes) {
+    const int r = t / kNodes, q = t - (t / kNodes) * kNodes;
+    const int gi = ta - 1 + r, gj = tb - 1 + q;
+    s_g[r][q] = (unsigned)gi < (unsigned)a.ny && (unsigned)gj < (unsigned)a.nx ? (G ? G[gi * a.nx + gj] : 1.0f) : 0.0f;
   }
-  int nly, nlx;
-  if (t < C::NNC) s_rfirst[t] = s_rlast[t] = -1;
-  const bool interior = ssd_prepare<STEP, TN>(a, U, ylo, xlo, RH, RWc, sh, nly, nlx);   // (ends with a barrier)
-  if (t < NCH) s_chb[t] = t * STEP < RWc ? sh.cb[t * STEP] : -100;
-  for (int i = t; i < RH; i += 256) {
-    const int rb = sh.rb[i];
-    if (i == 0 || sh.rb[i - 1] != rb) s_rfirst[rb] = i;
-    if (i == RH - 1 || sh.rb[i + 1] != rb) s_rlast[rb] = i;
-  }
-  // column weights towards the left and right node columns (one node
-  // column: all on the left)
-  for (int j = t; j < RWc; j += 256) {
-    const float f = sh.cf[j];
-    const float wr = a.nx > 1 ? f : 0.0f, wl = a.nx > 1 ? 1.0f - f : 1.0f;
-    s_cw[j] = make_float4(wr, wl, wr * wr, wl * wl);
-  }
-  // (the loss: a pixel counts at the tile holding its nearest node, whose
-  // support region holds it)
-  for (int i = t; kPart && i < RH + RWc; i += 256) {
-    const bool row = i < RH;
-    const int p = row ? ylo + i : xlo + (i - RH);
-    const int n = row ? a.ny : a.nx, lo = row ? ta : tb;
-    const int nn = min(max(fdiv(2 * p + 1, 2 * STEP), 0), n - 1);
-    const uint8_t o = nn >= lo && nn < lo + TN;
-    if (row) s_ownr[i] = o;
-    else s_ownc[i - RH] = o;
-  }
-  __syncthreads();
-  const int nchunks = (RWc + STEP - 1) / STEP;
-  // chunks start 16-byte aligned in A (frame base, row length and the
-  // region's first column multiples of four floats)
-  const bool a16 = (reinterpret_cast<uintptr_t>(A) & 15) == 0 && (a.W & 3) == 0 && (xlo & 3) == 0;
-  float lsum = 0.0f;   // this thread's share of the tile's loss (owned items)
-  for (int item = t; item < RH * nchunks; item += 256) {
-    const int i = item / nchunks, c = item - (item / nchunks) * nchunks;
-    const int y = ylo + i;
-    // windows holding row y: rows a0..a1; columns from the chunk
-    const int a0 = max(fdiv(y + h - STEP, STEP), 0), a1 = min(fdiv(y + h, STEP), a.ny - 1);
-    const int x0c = xlo + c * STEP;
-    const int b0 = max(fdiv(x0c + h - STEP, STEP), 0), b1 = min(fdiv(x0c + h, STEP), a.nx - 1);
-    float m = 0.0f;
-    for (int ii = a0; ii <= a1; ++ii)
-      for (int jj = b0; jj <= b1; ++jj) m += s_g[ii - gi0][jj - gj0];
-    float acc[8];
+  const bool interior = ssd_nodes(a, U, ta, tb, node);   // (ends with a barrier)
+  float lsum = 0.0f;   // this thread's share of the tile's loss (owned pixels)
+  auto columns = [&](auto in) {
+    constexpr bool kIn = decltype(in)::value;
+    ssd_deal(t, [&](int st, int j) __attribute__((always_inline)) {
+      const int kr = ta + st, cj = j / kStep, kc = tb + cj;
+      if (kr > tae + 1 || kc > tbe + 1) return;   // beyond the nodes' support
+      // windows kr - 1 and kr of the rows hold the strip, kc - 1 and kc of the columns
+      const float m = ((s_g[st][cj] + s_g[st][cj + 1]) + s_g[st + 1][cj]) + s_g[st + 1][cj + 1];
+      float acc[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) acc[k] = 0.0f;
-    const bool own = kPart && s_ownr[i];
-    float lacc = 0.0f;   // the loss terms r^2 of the chunk's pixels this tile counts
-    if (m != 0.0f) {
-      // the chunk's pixels share their node row and node columns (it starts
-      // on a cell boundary), so the node field is interpolated down the
-      // two node columns once and across per pixel
-      const int rb = sh.rb[i], cbase = s_chb[c];
-      const float fy = sh.rf[i];
-      const float uL = sh.node[0][rb][cbase] + fy * (sh.node[0][rb + 1][cbase] - sh.node[0][rb][cbase]);
-      const float uR = sh.node[0][rb][cbase + 1] + fy * (sh.node[0][rb + 1][cbase + 1] - sh.node[0][rb][cbase + 1]);
-      const float vL = sh.node[1][rb][cbase] + fy * (sh.node[1][rb + 1][cbase] - sh.node[1][rb][cbase]);
-      const float vR = sh.node[1][rb][cbase + 1] + fy * (sh.node[1][rb + 1][cbase + 1] - sh.node[1][rb][cbase + 1]);
-      // the pixels' terms without the chunk's common factor 2 m, which
-      // scales the sums once below; a whole chunk (every one when the
-      // region width is a multiple of STEP) runs without per-pixel tests,
-      // so its pixels' reads can be in flight together
-      const float xf0 = (float)x0c, yf = (float)y;
-      auto pixels = [&](auto inside) {
-        constexpr bool kIn = decltype(inside)::value;
-        auto px = [&](int e, float av) __attribute__((always_inline)) {
-          const int j = c * STEP + e;
-          const float4 w = s_cw[j];
-          float bs, gx, gy;
-          ssd_sample<kIn>(a, B, xf0 + (float)e, yf, uL + w.x * (uR - uL), vL + w.x * (vR - vL), bs, gx, gy);
-          const float r = bs - av;
-          const float t0 = r * gx, t1 = r * gy, t2 = gx * gx, t3 = gy * gy;
-          acc[0] += w.y * t0; acc[1] += w.x * t0;
-          acc[2] += w.y * t1; acc[3] += w.x * t1;
-          acc[4] += w.w * t2; acc[5] += w.z * t2;
-          acc[6] += w.w * t3; acc[7] += w.z * t3;
-          if constexpr (kPart) lacc += s_ownc[j] ? r * r : 0.0f;
-        };
-        if (kIn && a16 && (c + 1) * STEP <= RWc) {
-          // A's pixels of the chunk four at a time (16-byte aligned)
-          const float4* a4 = reinterpret_cast<const float4*>(reinterpret_cast<const char*>(A) +
-                                                             4u * (uint32_t)(y * a.W + x0c));
-#pragma unroll 1
-          for (int e4 = 0; e4 < STEP; e4 += 4) {
-            const float4 av = a4[e4 / 4];
-            px(e4, av.x);
-            px(e4 + 1, av.y);
-            px(e4 + 2, av.z);
-            px(e4 + 3, av.w);
+      for (int k = 0; k < 8; ++k) acc[k] = 0.0f;
+      if (m != 0.0f) {
+        const SsdCell row = ssd_cell_of(kr, a.ny, ta), col = ssd_cell_of(kc, a.nx, tb);
+        const int rb = kIn ? st : row.base, cb = kIn ? cj : col.base;
+        const float fx = ssd_fraction<kIn>(col, j & (kStep - 1));
+        const float u0 = node[0][rb][cb], u1 = node[0][rb][cb + 1];
+        const float du0 = node[0][rb + 1][cb] - u0, du1 = node[0][rb + 1][cb + 1] - u1;
+        const float v0 = node[1][rb][cb], v1 = node[1][rb][cb + 1];
+        const float dv0 = node[1][rb + 1][cb] - v0, dv1 = node[1][rb + 1][cb + 1] - v1;
+        float l0 = 0.0f, l1 = 0.0f;            // the loss of the strip's upper and lower half
+        ssd_column<kIn>(
+            a, A, B, kc * kStep - kStep / 2 + (j & (kStep - 1)), kr * kStep - kStep / 2,
+            [&](int e, float& u, float& v) {
+              const float fy = ssd_fraction<kIn>(row, e);
+              const float uL = u0 + fy * du0, uR = u1 + fy * du1;
+              const float vL = v0 + fy * dv0, vR = v1 + fy * dv1;
+              u = uL + fx * (uR - uL);
+              v = vL + fx * (vR - vL);
+            },
+            [&](int e, float r, float gx, float gy) {
+              const float f = ssd_fraction<kIn>(row, e);
+              const float wl = 1.0f - f, wr = f;
+              const float t0 = r * gx, t1 = r * gy, t2 = gx * gx, t3 = gy * gy;
+              acc[0] += wl * t0; acc[1] += wr * t0;
+              acc[2] += wl * t1; acc[3] += wr * t1;
+              acc[4] += (wl * wl) * t2; acc[5] += (wr * wr) * t2;
+              acc[6] += (wl * wl) * t3; acc[7] += (wr * wr) * t3;
+              if constexpr (kPart) (e < kStep / 2 ? l0 : l1) += r * r;
+            });
+        if constexpr (kPart) {
+          // a pixel counts at the tile of its nearest node: of row kr - 1 in
+          // the strip's upper half and kr in its lower (clamped to the grid),
+          // and so for the columns
+          const int nn = min(max(kc - ((j & (kStep - 1)) < kStep / 2 ? 1 : 0), 0), a.nx - 1);
+          const int n0 = min(max(kr - 1, 0), a.ny - 1), n1 = min(kr, a.ny - 1);
+          float lacc = 0.0f;
+          if (nn >= tb && nn < tb + kTile) {
+            if (n0 >= ta && n0 < ta + kTile) lacc += l0;
+            if (n1 >= ta && n1 < ta + kTile) lacc += l1;
+            lsum += m * lacc;
           }
-        } else if ((c + 1) * STEP <= RWc) {
-#pragma unroll 1
-          for (int e4 = 0; e4 < STEP; e4 += 4) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) px(e4 + e, ssd_a<kIn>(a, A, x0c + e4 + e, y));
-          }
-        } else {
-          for (int e = 0; e < STEP && c * STEP + e < RWc; ++e) px(e, ssd_a<kIn>(a, A, x0c + e, y));
         }
-      };
-      if (interior) pixels(std::true_type{});
-      else pixels(std::false_type{});
-    }
-    if (kPart && own) lsum += m * lacc;
-    const float m2 = 2.0f * m;
+      }
+      const float m2 = 2.0f * m;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) s_part[i][c][k] = m2 * acc[k];
-  }
+      for (int k = 0; k < 8; ++k) s_part[st * kPartStrip + k * kPartPlane + j] = m2 * acc[k];
+    });
+  };
+  if (interior) columns(std::true_type{});
+  else columns(std::false_type{});
   __syncthreads();
-  // pass 2: thread = (node, term); a node collects the left partials of the
-  // chunks based on its column and the right partials of the chunks based
-  // on the column before, weighted by its row weight
-  const int nd = t >> 2, term = t & 3;
-  const int na = ta + nd / TN, nb = tb + nd % TN;
+  // pass 2: thread = (node, term); a node collects the upper partials of the
+  // strips based on its row and the lower partials of the strips based on the
+  // row before, over the columns of the cells based on its column and on the
+  // column before with their weights
+  const int term = t & 3, nd = t >> 2;
+  const int na = ta + nd / kTile, nb = tb + (nd & (kTile - 1));
   float dsum = 0.0f;   // this thread's GN diagonal value (terms 2, 3)
-  if (nd < TN * TN && na < a.ny && nb < a.nx) {
-    const int cbn = nb - nlx;                          // node column in cache indices
-    const int rbn = na - nly;
+  if (na <= tae && nb <= tbe) {
     const bool sq = term >= 2;
-    // base rows and chunk bases do not decrease along the region: the rows
-    // and chunks that touch the node are contiguous runs (rows: those based
-    // on the node's row and, with more than one node row, on the row before)
-    int rf = RH, rl = -1, cf0 = nchunks, cl = -1;
-    if (rbn >= 0 && rbn < C::NNC && s_rfirst[rbn] >= 0) { rf = s_rfirst[rbn]; rl = s_rlast[rbn]; }
-    if (a.ny > 1 && rbn >= 1 && rbn - 1 < C::NNC && s_rfirst[rbn - 1] >= 0) {
-      rf = min(rf, s_rfirst[rbn - 1]);
-      rl = max(rl, s_rlast[rbn - 1]);
-    }
-    // the chunks based on the node's column (their left partials) and on
-    // the column before (their right partials), found once: one or two each
-    // (two where the region's edge chunks are clamped to the end cells;
-    // three when the grid is two nodes wide and every chunk has base 0); a
-    // missing one reads chunk 0 with weight 0
-    int lc[3] = {0, 0, 0}, rc[3] = {0, 0, 0};
-    float lw[3] = {0.0f, 0.0f, 0.0f}, rw[3] = {0.0f, 0.0f, 0.0f};
-    int nl = 0, nr = 0;
-    for (int c = 0; c < nchunks; ++c) {
-      const int base = s_chb[c];
-      if (base == cbn && nl < 3) { lc[nl] = c; lw[nl] = 1.0f; ++nl; }
-      if (a.nx > 1 && base + 1 == cbn && nr < 3) { rc[nr] = c; rw[nr] = 1.0f; ++nr; }
-    }
-    (void)cf0;
-    (void)cl;
     float s = 0.0f;
-    for (int i = rf; i <= rl; ++i) {
-      const int rb = sh.rb[i];
-      const float f = sh.rf[i];
-      float wy = 0.0f;
-      if (rb == rbn) wy += a.ny > 1 ? 1.0f - f : 1.0f;
-      if (a.ny > 1 && rb + 1 == rbn) wy += f;
-      float rowsum = 0.0f;
+    // cells kc and strips kr next to the node: n and n + 1, and at the grid's
+    // ends those clamped to the end nodes' cells
+    for (int kc = max(nb - 1, tb); kc <= min(nb + 2, tbe + 1); ++kc) {
+      const SsdCell col = ssd_cell_of(kc, a.nx, 1);
+      const bool left = col.base == nb, right = a.nx > 1 && col.base + 1 == nb;
+      if (!left && !right) continue;
+      float c[kStep];
 #pragma unroll
-      for (int q = 0; q < 3; ++q)
-        rowsum += lw[q] * s_part[i][lc[q]][2 * term] + rw[q] * s_part[i][rc[q]][2 * term + 1];
-      s += (sq ? wy * wy : wy) * rowsum;
+      for (int e = 0; e < kStep; ++e) c[e] = 0.0f;
+      for (int kr = max(na - 1, ta); kr <= min(na + 2, tae + 1); ++kr) {
+        const SsdCell row = ssd_cell_of(kr, a.ny, 1);
+        const bool up = row.base == na, low = a.ny > 1 && row.base + 1 == na;
+        if (!up && !low) continue;
+        const float* q = &s_part[(kr - ta) * kPartStrip + (2 * term + (up ? 0 : 1)) * kPartPlane + (kc - tb) * kStep];
+#pragma unroll
+        for (int e = 0; e < kStep; ++e) c[e] += q[e];
+      }
+#pragma unroll
+      for (int e = 0; e < kStep; ++e) {
+        const float f = col.f0 + (float)e * col.df;
+        const float w = left ? 1.0f - f : f;
+        s += (sq ? w * w : w) * c[e];
+      }
     }
     const int idx = na * a.nx + nb;
     if (term < 2) {
@@ -647,7 +622,7 @@ __global__ __launch_bounds__(256) void k_ssd_backward_t(SsdArgs a) {
     const float ls = tile_sum(lsum, s_red);
     const float ds = tile_sum(dsum, s_red);
     if (t == 0) {
-      float* o = a.part + (int64_t)pair * a.pstride + 2 * (wg.y * ((a.nx + TN - 1) / TN) + wg.x);
+      float* o = a.part + (int64_t)pair * a.pstride + 2 * (wg.y * ((a.nx + kTile - 1) / kTile) + wg.x);
       o[0] = ds;
       o[1] = ls;
     }
@@ -771,7 +746,7 @@ hipError_t launch_ssd_forward(const Plan& P, const float* A, const float* B, con
   // tile: at most 8 x 8 windows with a pixel region of at most 96 x 96
   if (a.step == 8 && a.win == 16) {
     dim3 grid((a.nx + 7) / 8, (a.ny + 7) / 8, n);
-    hipLaunchKernelGGL((k_ssd_forward_t<8, 8>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_ssd_forward_t, grid, dim3(256), 0, s, a);
     return hipGetLastError();
   }
   int TN = max(1, min(8, (96 - a.win) / a.step + 1));
@@ -795,7 +770,7 @@ hipError_t launch_ssd_backward(const Plan& P, const float* A, const float* B, co
   }
   if (a.step == 8 && a.win == 16) {
     dim3 grid((a.nx + 7) / 8, (a.ny + 7) / 8, n);
-    hipLaunchKernelGGL((k_ssd_backward_t<8, 8, false>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_ssd_backward_t<false>), grid, dim3(256), 0, s, a);
     return hipGetLastError();
   }
   // 16 threads per node -> 16 nodes per workgroup; support region of a
@@ -821,7 +796,7 @@ hipError_t launch_ssd_refine_step(const Plan& P, const float* A, const float* B,
   a.part = reinterpret_cast<float*>(P.ws + P.off_part);
   a.pstride = a.gstride;
   dim3 grid((a.nx + 7) / 8, (a.ny + 7) / 8, n);
-  hipLaunchKernelGGL((k_ssd_backward_t<8, 8, true>), grid, dim3(256), 0, s, a);
+  hipLaunchKernelGGL((k_ssd_backward_t<true>), grid, dim3(256), 0, s, a);
   if (hipError_t e = hipGetLastError()) return e;
   const int np = P.nx * P.ny;
   const int ntiles = (int)(grid.x * grid.y);
