@@ -705,7 +705,8 @@ __global__ __launch_bounds__(64 * ((2 * R + DYG) / DYG)) void k_sad_cells16(SadA
 // Finer-level SAD search with cell-shared sums for u16 frames (block =
 // 2 step, step 12, R <= 2): the four children of a parent share a 3x3 group
 // of 12x12 cells (9 cell SADs per shift instead of 16).  Lane = cell of a
-// parent's group (7 parents per wave); the lane streams its 12 A rows
+// parent's group (7 parents per wave, counted along the rows, so that a row's
+// end leaves no lanes idle); the lane streams its 12 A rows
 // through a ring of 2R + 1 and the 12 + 2R B rows once, v_sad_u16 on
 // realigned words (an odd shift column is a 2-byte realignment).  A child's
 // sums: its cell + the right-hand cell (DPP lane + 1) + the pair below (lane
@@ -720,13 +721,12 @@ __global__ __launch_bounds__(256) void k_sad_cells16_fine(SadArgs g) {
   const int pair = wg.z;
   if (slot_off(g.mask, pair)) return;
   const int pnx = (g.nx + 1) / 2, pny = (g.ny + 1) / 2;
-  const int ntx = (pnx + PPW - 1) / PPW;
-  const int tile = wg.x * 4 + (threadIdx.x >> 6);
-  if (tile >= ntx * pny) return;   // a whole wave (no barriers below)
-  const int pa = tile / ntx, tx = tile - pa * ntx;
+  const int p0 = (wg.x * 4 + (threadIdx.x >> 6)) * PPW;   // the wave's first parent, counted along the rows
+  if (p0 >= pnx * pny) return;   // a whole wave (no barriers below)
   const int grp = min(lane / 9, PPW - 1), cell = lane - 9 * (lane / 9);
   const int u = cell / 3, v = cell - 3 * (cell / 3);
-  const int pb = min(tx * PPW + grp, pnx - 1);
+  const int p = min(p0 + grp, pnx * pny - 1);
+  const int pa = p / pnx, pb = p - pa * pnx;
   const int32_t* par = g.parent + (int64_t)pair * g.pstride;
   int cx, cy;
   parent_centre(g, par, min(pa, g.pny - 1), min(pb, g.pnx - 1), cx, cy);
@@ -789,7 +789,7 @@ __global__ __launch_bounds__(256) void k_sad_cells16_fine(SadArgs g) {
     __builtin_amdgcn_sched_barrier(0);
   }
   const int a = 2 * pa + u, b = 2 * pb + v;
-  if (lane < 9 * PPW && u < 2 && v < 2 && tx * PPW + lane / 9 < pnx && a < g.ny && b < g.nx) {
+  if (lane < 9 * PPW && u < 2 && v < 2 && p0 + lane / 9 < pnx * pny && a < g.ny && b < g.nx) {
     int32_t* out = g.out + (int64_t)pair * g.ostride;
     out[a * g.nx + b] = (int)(best & 0xff) - 128;
     out[g.nx * g.ny + a * g.nx + b] = (int)((best >> 8) & 0xff) - 128;
@@ -803,7 +803,9 @@ __global__ __launch_bounds__(256) void k_sad_cells16_fine(SadArgs g) {
 // a 3x3 group of 8x8 cells: 9 cell SADs per shift instead of 16, four shift
 // columns per quad SAD (16-bit fields: a cell is at most 64 x 255, four
 // cells stay below 2^16).  Lane = (parent, cell column), 21 parents per
-// wave: the lane streams the 24 A rows and 24 + 2R B rows of its column once
+// wave, counted along the rows of the grid (with waves that end at a row's
+// end, a row of 64 parents takes four waves for three: bound by VALU issue,
+// level 0 of 64 pairs of 1 MP then took 65 us instead of 54): the lane streams the 24 A rows and 24 + 2R B rows of its column once
 // (A rows in a ring, both read ahead), keeps the SADs of its three cells, and
 // forms its two children's sums as (cell + the cell below, a register add) +
 // the same pair of the right-hand column (DPP lane + 1).  The parent's
@@ -824,12 +826,11 @@ __global__ __launch_bounds__(256) void k_sad_cols(SadArgs g) {
   const int pair = wg.z;
   if (slot_off(g.mask, pair)) return;
   const int pnx = (g.nx + 1) / 2, pny = (g.ny + 1) / 2;
-  const int ntx = (pnx + PPW - 1) / PPW;
-  const int tile = wg.x * 4 + (threadIdx.x >> 6);
-  if (tile >= ntx * pny) return;   // a whole wave (no barriers below)
-  const int pa = tile / ntx, tx = tile - pa * ntx;
+  const int p0 = (wg.x * 4 + (threadIdx.x >> 6)) * PPW;   // the wave's first parent, counted along the rows
+  if (p0 >= pnx * pny) return;   // a whole wave (no barriers below)
   const int grp = min(lane / 3, PPW - 1), v = lane - 3 * (lane / 3);
-  const int pb = min(tx * PPW + grp, pnx - 1);
+  const int p = min(p0 + grp, pnx * pny - 1);
+  const int pa = p / pnx, pb = p - pa * pnx;
   const int32_t* par = g.parent + (int64_t)pair * g.pstride;
   int cx, cy;
   parent_centre(g, par, min(pa, g.pny - 1), min(pb, g.pnx - 1), cx, cy);
@@ -949,7 +950,7 @@ __global__ __launch_bounds__(256) void k_sad_cols(SadArgs g) {
     }
   }
   const int b = 2 * pb + v;
-  const bool col = lane < 3 * PPW && v < 2 && tx * PPW + lane / 3 < pnx && b < g.nx;
+  const bool col = lane < 3 * PPW && v < 2 && p0 + lane / 3 < pnx * pny && b < g.nx;
   int32_t* out = g.out + (int64_t)pair * g.ostride;
 #pragma unroll
   for (int uc = 0; uc < 2; ++uc) {
@@ -1925,7 +1926,7 @@ hipError_t launch_sad_level(const Plan& P, int l, const void* A, const void* B, 
   const int NW = P.block * P.es / 4;
   // finer levels, u16, 24x24 blocks at step 12, R <= 2: cell-shared sums per parent
   if (g.parent && P.es == 2 && P.p.step == 12 && P.block == 24 && g.R >= 1 && g.R <= 2) {
-    const int tiles = (((v.nx + 1) / 2 + 6) / 7) * ((v.ny + 1) / 2);
+    const int tiles = (((v.nx + 1) / 2) * ((v.ny + 1) / 2) + 6) / 7;
     const dim3 grid((tiles + 3) / 4, 1, n);
     if (g.R == 2) hipLaunchKernelGGL((k_sad_cells16_fine<2>), grid, dim3(256), 0, s, g);
     else hipLaunchKernelGGL((k_sad_cells16_fine<1>), grid, dim3(256), 0, s, g);
@@ -1942,7 +1943,7 @@ hipError_t launch_sad_level(const Plan& P, int l, const void* A, const void* B, 
   // finer levels, u8, 16x16 blocks at step 8, R <= 2: cell-shared sums per parent
   if (g.parent && P.es == 1 && P.p.step == 8 && P.block == 16 && g.R >= 1 && g.R <= 2 &&
       (size_t)v.rows * v.pitch < (1u << 31) && v.pitch < (1 << 24)) {
-    const int tiles3 = (((v.nx + 1) / 2 + 20) / 21) * ((v.ny + 1) / 2);
+    const int tiles3 = (((v.nx + 1) / 2) * ((v.ny + 1) / 2) + 20) / 21;
     const dim3 grid3((tiles3 + 3) / 4, 1, n);
     if (g.R == 2) hipLaunchKernelGGL((k_sad_cols<2>), grid3, dim3(256), 0, s, g);
     else hipLaunchKernelGGL((k_sad_cols<1>), grid3, dim3(256), 0, s, g);
