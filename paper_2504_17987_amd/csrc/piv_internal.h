@@ -79,6 +79,8 @@ hipError_t launch_uod(const Plan& P, const float* src, int64_t sstride, float* d
                       int n, hipStream_t s);
 // level-0 predictor field (through the median) -> validated float predictor
 hipError_t launch_pred_validate(const Plan& P, int n, float* pred, hipStream_t s);
+hipError_t launch_uod_vorticity(const Plan& P, const float* src, int64_t sstride, float* dst, uint8_t* flags,
+                                float* omega, int n, hipStream_t s);
 hipError_t launch_vorticity(const Plan& P, const float* disp, float* omega, int n, hipStream_t s);
 hipError_t launch_ssd_forward(const Plan& P, const float* A, const float* B, const float* U, int n,
                               float* loss, hipStream_t s);

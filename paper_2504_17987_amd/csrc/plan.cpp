@@ -306,11 +306,13 @@ piv_status run_path(const Plan& P, const void* A, const void* B, int64_t pitch, 
   if (piv_status s = dev(piv::launch_correct(P, A, B, pitch, n, pred, raw, peak, flags, stream, rstride),
                          "correct"))
     return s;
+  if (!tm || !tm->state_disp)
+    return dev(piv::launch_uod_vorticity(P, raw, rstride, disp, flags, omega, n, stream), "validate_vorticity");
+  // (the vorticity is that of the smoothed field)
   if (piv_status s = dev(piv::launch_uod(P, raw, rstride, disp, flags, n, stream), "validate")) return s;
-  if (tm && tm->state_disp)
-    if (piv_status s = dev(piv::launch_smooth(P, disp, tm->state_disp, tm->slot, tm->nstate, tm->alpha2, n,
-                                              stream), "smooth_disp"))
-      return s;
+  if (piv_status s = dev(piv::launch_smooth(P, disp, tm->state_disp, tm->slot, tm->nstate, tm->alpha2, n,
+                                            stream), "smooth_disp"))
+    return s;
   return dev(piv::launch_vorticity(P, disp, omega, n, stream), "vorticity");
 }
 

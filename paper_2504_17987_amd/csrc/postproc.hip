@@ -23,15 +23,20 @@ constexpr uint8_t kInvalid = PIV_F_FLAT | PIV_F_BORDER;
 // source, so that no workgroup reads what another one writes.
 constexpr int TW = 64, TH = 16;             // tile; one thread per vector
 constexpr int NT = TW * TH;
-constexpr int E1W = TW + 2, E1H = TH + 2;   // detection region: tile + 1 ring
-constexpr int E2W = TW + 4, E2H = TH + 4;   // staged field: tile + 2 rings
+constexpr int E2W = TW + 4, E2H = TH + 4;   // tile + 2 rings
 
+// The field staged with RING rings, detection with one fewer, replacement
+// with two fewer (RING 2: the tile; RING 3, where the vorticity follows: the
+// tile and the ring that its differences reach into).
+template <int RING>
 struct UodTile {
-  float u[E2H][E2W], v[E2H][E2W];
-  uint8_t ok[E2H][E2W];    // in the grid and not FLAT/BORDER
-  uint8_t out[E1H][E1W];   // 1: outlier or outside the grid (never a usable neighbour)
-  int n_out;               // outliers of the tile (the caller zeroes it before its barrier)
-  uint16_t list[NT];       // their tile positions, in no particular order
+  static constexpr int SW = TW + 2 * RING, SH = TH + 2 * RING;               // staged
+  static constexpr int DW = SW - 2, DH = SH - 2, LW = SW - 4, LH = SH - 4;   // detected, replaced
+  float u[SH][SW], v[SH][SW];
+  uint8_t ok[SH][SW];        // in the grid and not FLAT/BORDER
+  uint8_t out[DH][DW];       // 1: outlier or outside the grid (never a usable neighbour)
+  int n_out;                 // outliers to replace (the caller zeroes it before its barrier)
+  uint16_t list[LW * LH];    // their positions in the replaced region, in no particular order
 };
 
 __device__ __forceinline__ int clampi(int v, int hi) { return min(max(v, 0), hi); }
@@ -65,15 +70,14 @@ __device__ __forceinline__ bool uod_component_out(float (&s)[8], int k, float x,
   return fabsf(x - um) > thr * (rm + eps);
 }
 
-// Detection and replacement on a staged tile (the caller has filled u, v, ok
-// and passed a barrier).  dst: the pair's output field [2][ny][nx]; fl: the
-// pair's flags (nullable).
-__device__ __forceinline__ void uod_tile(UodTile& T, int x0, int y0, int nx, int ny, float thr,
-                                         float eps, float* dst, uint8_t* fl) {
-  const int t = threadIdx.x;
-  for (int idx = t; idx < E1H * E1W; idx += NT) {
-    const int r = idx / E1W, c = idx - r * E1W;
-    const int y = y0 - 1 + r, x = x0 - 1 + c;
+// Detection on a staged tile (the caller has filled u, v, ok and passed a
+// barrier); ends with a barrier.
+template <int RING>
+__device__ __forceinline__ void uod_detect(UodTile<RING>& T, int x0, int y0, int nx, int ny, float thr, float eps) {
+  using D = UodTile<RING>;
+  for (int idx = threadIdx.x; idx < D::DH * D::DW; idx += NT) {
+    const int r = idx / D::DW, c = idx - r * D::DW;
+    const int y = y0 - (RING - 1) + r, x = x0 - (RING - 1) + c;
     uint8_t o = 1;
     if (y >= 0 && x >= 0 && y < ny && x < nx && T.ok[r + 1][c + 1]) {
       // neighbours in static slots; unusable ones hold a sentinel that sorts last
@@ -97,11 +101,44 @@ __device__ __forceinline__ void uod_tile(UodTile& T, int x0, int y0, int nx, int
         o = 0;
     }
     T.out[r][c] = o;
-    // outliers of the tile itself are replaced below, by consecutive threads
-    if (o && r >= 1 && r <= TH && c >= 1 && c <= TW && y < ny && x < nx)
-      T.list[atomicAdd(&T.n_out, 1)] = (uint16_t)((r - 1) * TW + c - 1);
+    // outliers are replaced afterwards, by consecutive threads
+    if (o && r >= 1 && r <= D::LH && c >= 1 && c <= D::LW && y >= 0 && x >= 0 && y < ny && x < nx)
+      T.list[atomicAdd(&T.n_out, 1)] = (uint16_t)((r - 1) * D::LW + c - 1);
   }
   __syncthreads();
+}
+
+// The replacement (ru, rv) of the outlier at (r, c) of the replaced region,
+// its own value if there is none; returns its flags.
+template <int RING>
+__device__ __forceinline__ uint8_t uod_replacement(const UodTile<RING>& T, int r, int c, float& ru, float& rv) {
+  float vu[8], vv[8];
+  int k = 0, slot = 0;
+#pragma unroll
+  for (int di = 0; di < 3; ++di)
+#pragma unroll
+    for (int dj = 0; dj < 3; ++dj) {
+      if (di == 1 && dj == 1) continue;
+      const bool ok = !T.out[r + di][c + dj];
+      vu[slot] = ok ? T.u[r + 1 + di][c + 1 + dj] : kSlotF;
+      vv[slot] = ok ? T.v[r + 1 + di][c + 1 + dj] : kSlotF;
+      k += ok;
+      ++slot;
+    }
+  ru = T.u[r + 2][c + 2];
+  rv = T.v[r + 2][c + 2];
+  if (k == 0) return PIV_F_OUTLIER | PIV_F_UNRESOLVED;
+  ru = median8_f(vu, k);
+  rv = median8_f(vv, k);
+  return PIV_F_OUTLIER | PIV_F_REPLACED;
+}
+
+// Detection and replacement on a staged tile.  dst: the pair's output field
+// [2][ny][nx]; fl: the pair's flags (nullable).
+__device__ __forceinline__ void uod_tile(UodTile<2>& T, int x0, int y0, int nx, int ny, float thr,
+                                         float eps, float* dst, uint8_t* fl) {
+  const int t = threadIdx.x;
+  uod_detect(T, x0, y0, nx, ny, thr, eps);
   const int np = nx * ny;
   {
     const int ty = t / TW, tx = t - ty * TW, y = y0 + ty, x = x0 + tx;
@@ -113,32 +150,45 @@ __device__ __forceinline__ void uod_tile(UodTile& T, int x0, int y0, int nx, int
   const int n_out = T.n_out;
   for (int j = t; j < n_out; j += NT) {
     const int p = T.list[j], ty = p / TW, tx = p - ty * TW, i = (y0 + ty) * nx + x0 + tx;
-    float vu[8], vv[8];
-    int k = 0, slot = 0;
-#pragma unroll
-    for (int di = 0; di < 3; ++di)
-#pragma unroll
-      for (int dj = 0; dj < 3; ++dj) {
-        if (di == 1 && dj == 1) continue;
-        const bool ok = !T.out[ty + di][tx + dj];
-        vu[slot] = ok ? T.u[ty + 1 + di][tx + 1 + dj] : kSlotF;
-        vv[slot] = ok ? T.v[ty + 1 + di][tx + 1 + dj] : kSlotF;
-        k += ok;
-        ++slot;
-      }
-    float ru = T.u[ty + 2][tx + 2], rv = T.v[ty + 2][tx + 2];
-    uint8_t f = PIV_F_OUTLIER;
-    if (k == 0) {
-      f |= PIV_F_UNRESOLVED;
-    } else {
-      ru = median8_f(vu, k);
-      rv = median8_f(vv, k);
-      f |= PIV_F_REPLACED;
-    }
+    float ru, rv;
+    const uint8_t f = uod_replacement(T, ty, tx, ru, rv);
     if (fl) fl[i] |= f;
     dst[i] = ru;
     dst[np + i] = rv;
   }
+}
+
+// Stages the field S and, with HAS_FL, its flags' usable vectors on the tile
+// and RING rings; ends with a barrier.
+template <int RING, bool HAS_FL>
+__device__ __forceinline__ void uod_stage(UodTile<RING>& T, const float* S, const uint8_t* FL, int x0, int y0, int nx,
+                                          int ny) {
+  using D = UodTile<RING>;
+  const int t = threadIdx.x, np = nx * ny;
+  // every load first (clamped, always valid addresses), then the LDS stores
+  constexpr int NE = D::SH * D::SW, NP = (NE + NT - 1) / NT;
+  float lu[NP], lv[NP];
+  uint8_t lf[NP];
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const int idx = t + NT * q, r = idx / D::SW, c = idx - r * D::SW;
+    const int o = clampi(y0 - RING + r, ny - 1) * nx + clampi(x0 - RING + c, nx - 1);
+    lu[q] = S[o];
+    lv[q] = S[np + o];
+    lf[q] = HAS_FL ? FL[o] : 0;
+  }
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const int idx = t + NT * q, r = idx / D::SW, c = idx - r * D::SW;
+    if (idx < NE) {
+      const int y = y0 - RING + r, x = x0 - RING + c;
+      T.u[r][c] = lu[q];
+      T.v[r][c] = lv[q];
+      T.ok[r][c] = y >= 0 && x >= 0 && y < ny && x < nx && !(lf[q] & kInvalid);
+    }
+  }
+  if (t == 0) T.n_out = 0;
+  __syncthreads();
 }
 
 // Validation of src (pair stride sstride floats) into dst ([n][2][ny][nx]).
@@ -149,37 +199,13 @@ template <bool HAS_FL>
 __global__ __launch_bounds__(NT) void k_uod(const float* src, int64_t sstride, float* dst,
                                              uint8_t* flags, int nx, int ny, float thr, float eps,
                                              const uint8_t* smask) {
-  __shared__ UodTile T;
+  __shared__ UodTile<2> T;
   const int pair = blockIdx.z;
   if (slot_off(smask, pair)) return;
-  const int x0 = blockIdx.x * TW, y0 = blockIdx.y * TH, t = threadIdx.x;
+  const int x0 = blockIdx.x * TW, y0 = blockIdx.y * TH;
   const int np = nx * ny;
-  const float* S = src + (int64_t)pair * sstride;
   uint8_t* FL = HAS_FL ? flags + (int64_t)pair * np : nullptr;
-  // every load first (clamped, always valid addresses), then the LDS stores
-  constexpr int NE = E2H * E2W, NP = (NE + NT - 1) / NT;
-  float lu[NP], lv[NP];
-  uint8_t lf[NP];
-#pragma unroll
-  for (int q = 0; q < NP; ++q) {
-    const int idx = t + NT * q, r = idx / E2W, c = idx - r * E2W;
-    const int o = clampi(y0 - 2 + r, ny - 1) * nx + clampi(x0 - 2 + c, nx - 1);
-    lu[q] = S[o];
-    lv[q] = S[np + o];
-    lf[q] = HAS_FL ? FL[o] : 0;
-  }
-#pragma unroll
-  for (int q = 0; q < NP; ++q) {
-    const int idx = t + NT * q, r = idx / E2W, c = idx - r * E2W;
-    if (idx < NE) {
-      const int y = y0 - 2 + r, x = x0 - 2 + c;
-      T.u[r][c] = lu[q];
-      T.v[r][c] = lv[q];
-      T.ok[r][c] = y >= 0 && x >= 0 && y < ny && x < nx && !(lf[q] & kInvalid);
-    }
-  }
-  if (t == 0) T.n_out = 0;
-  __syncthreads();
+  uod_stage<2, HAS_FL>(T, src + (int64_t)pair * sstride, FL, x0, y0, nx, ny);
   uod_tile(T, x0, y0, nx, ny, thr, eps, dst + (int64_t)pair * 2 * np, FL);
 }
 
@@ -191,7 +217,7 @@ __global__ __launch_bounds__(NT) void k_pred_uod(const int32_t* d, int64_t dstri
                                                   const uint8_t* smask) {
   constexpr int E3W = TW + 6, E3H = TH + 6, NE = E3H * E3W, NP = (NE + NT - 1) / NT;
   __shared__ int sd[2][E3H][E3W];
-  __shared__ UodTile T;
+  __shared__ UodTile<2> T;
   const int pair = blockIdx.z;
   if (slot_off(smask, pair)) return;
   const int x0 = blockIdx.x * TW, y0 = blockIdx.y * TH, t = threadIdx.x;
@@ -243,12 +269,13 @@ __global__ __launch_bounds__(NT) void k_pred_uod(const int32_t* d, int64_t dstri
   uod_tile(T, x0, y0, nx, ny, thr, eps, pred + (int64_t)pair * 2 * np, nullptr);
 }
 
+// Derivative along a line of n vectors at its vector i, which f points at.
 __device__ __forceinline__ float dline(const float* f, int n, int stride, int i, float h) {
   if (n == 1) return 0.0f;
-  if (n == 2) return (f[stride] - f[0]) / h;
+  if (n == 2) return i == 0 ? (f[stride] - f[0]) / h : (f[0] - f[-stride]) / h;
   if (i == 0) return (-3.0f * f[0] + 4.0f * f[stride] - f[2 * stride]) / (2.0f * h);
-  if (i == n - 1) return (3.0f * f[i * stride] - 4.0f * f[(i - 1) * stride] + f[(i - 2) * stride]) / (2.0f * h);
-  return (f[(i + 1) * stride] - f[(i - 1) * stride]) / (2.0f * h);
+  if (i == n - 1) return (3.0f * f[0] - 4.0f * f[-stride] + f[-2 * stride]) / (2.0f * h);
+  return (f[stride] - f[-stride]) / (2.0f * h);
 }
 
 __global__ __launch_bounds__(256) void k_vorticity(const float* disp, float* omega, int nx, int ny,
@@ -261,8 +288,56 @@ __global__ __launch_bounds__(256) void k_vorticity(const float* disp, float* ome
   const int a = i / nx, b = i - a * nx;
   const float* U = disp + (int64_t)pair * 2 * np;
   const float* V = U + np;
-  float dvdx = dline(V + a * nx, nx, 1, b, h);
-  float dudy = dline(U + b, ny, nx, a, h);
+  float dvdx = dline(V + i, nx, 1, b, h);
+  float dudy = dline(U + i, ny, nx, a, h);
+  omega[(int64_t)pair * np + i] = dvdx - dudy;
+}
+
+// Validation of src into dst as k_uod<true>, with the vorticity of the result:
+// the ring of vectors around the tile is replaced too, so that the
+// differences find it in LDS.  The last tile of a row or column moves back to
+// end with the grid, so that the one-sided differences at the grid's ends
+// find their three vectors in it (vectors of two tiles are written twice, with
+// the same values).  Bound by the latency of its phases for one pair (128 x
+// 128 vectors 7.5 us against 6.4 + 3.9 us for the two kernels)
+// and by VALU issue for many (64 pairs 21.8 us against 18.4 + 6.1 us).
+__global__ __launch_bounds__(NT) void k_uod_vorticity(const float* src, int64_t sstride, float* dst, uint8_t* flags,
+                                                      float* omega, int nx, int ny, float thr, float eps, float h,
+                                                      const uint8_t* smask) {
+  using D = UodTile<3>;
+  __shared__ D T;
+  __shared__ float rep[2][D::LW * D::LH];   // the listed outliers' replacements
+  const int pair = blockIdx.z;
+  if (slot_off(smask, pair)) return;
+  const int x0 = min((int)blockIdx.x * TW, max(nx - TW, 0)), y0 = min((int)blockIdx.y * TH, max(ny - TH, 0));
+  const int t = threadIdx.x, np = nx * ny;
+  uint8_t* FL = flags + (int64_t)pair * np;
+  uod_stage<3, true>(T, src + (int64_t)pair * sstride, FL, x0, y0, nx, ny);
+  uod_detect(T, x0, y0, nx, ny, thr, eps);
+  const int n_out = T.n_out;
+  for (int j = t; j < n_out; j += NT) {
+    const int p = T.list[j], r = p / D::LW, c = p - r * D::LW;
+    float ru, rv;
+    const uint8_t f = uod_replacement(T, r, c, ru, rv);
+    rep[0][j] = ru;
+    rep[1][j] = rv;
+    if (r >= 1 && r <= TH && c >= 1 && c <= TW) FL[(y0 + r - 1) * nx + x0 + c - 1] |= f;
+  }
+  __syncthreads();   // (every replacement is formed from the field as it was)
+  for (int j = t; j < n_out; j += NT) {
+    const int p = T.list[j], r = p / D::LW, c = p - r * D::LW;
+    T.u[r + 2][c + 2] = rep[0][j];
+    T.v[r + 2][c + 2] = rep[1][j];
+  }
+  __syncthreads();
+  const int ty = t / TW, tx = t - ty * TW, y = y0 + ty, x = x0 + tx;
+  if (y >= ny || x >= nx) return;
+  const int i = y * nx + x;
+  const float *u = &T.u[ty + 3][tx + 3], *v = &T.v[ty + 3][tx + 3];
+  float* o = dst + (int64_t)pair * 2 * np;
+  o[i] = *u;
+  o[np + i] = *v;
+  const float dvdx = dline(v, nx, 1, x, h), dudy = dline(u, ny, D::SW, y, h);
   omega[(int64_t)pair * np + i] = dvdx - dudy;
 }
 
@@ -311,6 +386,14 @@ hipError_t launch_uod(const Plan& P, const float* src, int64_t sstride, float* d
   else
     hipLaunchKernelGGL(k_uod<false>, grid, dim3(NT), 0, s, src, sstride, dst, flags, P.nx, P.ny,
                        P.p.uod_threshold, P.p.uod_epsilon, P.slot_mask);
+  return hipGetLastError();
+}
+
+hipError_t launch_uod_vorticity(const Plan& P, const float* src, int64_t sstride, float* dst, uint8_t* flags,
+                                float* omega, int n, hipStream_t s) {
+  dim3 grid((P.nx + TW - 1) / TW, (P.ny + TH - 1) / TH, n);
+  hipLaunchKernelGGL(k_uod_vorticity, grid, dim3(NT), 0, s, src, sstride, dst, flags, omega, P.nx, P.ny,
+                     P.p.uod_threshold, P.p.uod_epsilon, (float)P.p.step, P.slot_mask);
   return hipGetLastError();
 }
 
