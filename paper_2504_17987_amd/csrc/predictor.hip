@@ -464,7 +464,11 @@ constexpr int sad_passes() { return (2 * R + 1 + DYG - 1) / DYG; }
 // below (lane + 9); four cells stay below 2^16, so the packed fields add
 // without carries.  Winner: the least (SAD, |dx|+|dy|, dy, dx).  A
 // workgroup is one tile; its waves take the passes side by side (a coarse
-// level has few tiles) and the first wave merges their winners.
+// level has few tiles) and the first wave merges their winners.  Bound by the
+// latency of its rows for one pair and by VALU issue for many: passes of four
+// shift rows with the B rows read four ahead take 6.4 us for one pair of 1 MP
+// (R 6) and 18.8 for 64, passes of seven reading each row at its use took
+// 11.2 and 23 (seven with the read ahead 8.2 and 22.8, three 5.9 and 20.6).
 // ---------------------------------------------------------------------------
 template <int R, int DYG, bool kCost = false>
 __global__ __launch_bounds__(64 * ((2 * R + DYG) / DYG)) void k_sad_cells(SadArgs g) {
@@ -519,12 +523,21 @@ __global__ __launch_bounds__(64 * ((2 * R + DYG) / DYG)) void k_sad_cells(SadArg
       for (int m = 0; m < (NQ > 0 ? NQ : 1); ++m) acc[k][m] = 0ull;
       tacc[k][0] = tacc[k][1] = 0u;
     }
+    // B rows are read PF ahead of their use (past the pass, its last row again)
+    constexpr int PF = 4;
+    auto brow = [&](int rb) {
+      const unsigned o = boff + (unsigned)(k0 + min(rb, 8 + nk - 2)) * pitch32;
+      return *reinterpret_cast<const Words<RW + 1>*>(Bp + (size_t)o);
+    };
+    Words<RW + 1> bring[PF];
+#pragma unroll
+    for (int i = 0; i < PF; ++i) bring[i] = brow(i);
 #pragma unroll
     for (int rb = 0; rb < 8 + DYG - 1; ++rb) {
       if (rb >= 8 + nk - 1) continue;
       // B row y + (k0 - R) + rb: it meets A row rb - k for shift row k0 + k
-      const Words<RW + 1> wv =
-          *reinterpret_cast<const Words<RW + 1>*>(Bp + (size_t)(boff + (unsigned)(k0 + rb) * pitch32));
+      const Words<RW + 1> wv = bring[rb % PF];
+      if (rb + PF < 8 + DYG - 1) bring[rb % PF] = brow(rb + PF);
       uint32_t rw[RW];
 #pragma unroll
       for (int i = 0; i < RW; ++i) rw[i] = __builtin_amdgcn_alignbyte(wv.w[i + 1], wv.w[i], sh);
@@ -712,6 +725,9 @@ __global__ __launch_bounds__(64 * ((2 * R + DYG) / DYG)) void k_sad_cells16(SadA
 // sums: its cell + the right-hand cell (DPP lane + 1) + the pair below (lane
 // permute, lane + 3).  Level 0 reads in place as in k_sad_stream.  Winner:
 // the least (SAD, |dx|+|dy|, dy, dx).
+// Bound by VALU issue (1,800 v_sad_u16 of 2,850 operations a wave, or 81 us of
+// level 0 of 8 pairs of 9 MP): 97 us with the rows read two ahead of their use,
+// 104 with each read at its use.
 // ---------------------------------------------------------------------------
 template <int R>
 __global__ __launch_bounds__(256) void k_sad_cells16_fine(SadArgs g) {
@@ -747,12 +763,22 @@ __global__ __launch_bounds__(256) void k_sad_cells16_fine(SadArgs g) {
   for (int q = 0; q < G; ++q)
 #pragma unroll
     for (int c = 0; c < G; ++c) acc[q][c] = 0u;
-  Words<CWD> aring[G];   // A row r sits in aring[r % G]
+  constexpr int PF = 2;   // rows read ahead of their use
+  auto arow = [&](int r) { return *reinterpret_cast<const Words<CWD>*>(Ab + (int64_t)r * apitch); };
+  auto brow = [&](int r) { return *reinterpret_cast<const Words<RW + 1>*>(Bb + (int64_t)r * bpitch); };
+  Words<CWD> aring[G + PF];   // A row r sits in aring[r % (G + PF)]
+  Words<RW + 1> bring[PF];
+#pragma unroll
+  for (int i = 0; i < PF; ++i) {
+    aring[i] = arow(i);
+    bring[i] = brow(i);
+  }
 #pragma unroll
   for (int rb = 0; rb < 12 + 2 * R; ++rb) {
-    if (rb < 12) aring[rb % G] = *reinterpret_cast<const Words<CWD>*>(Ab + (int64_t)rb * apitch);
     // B row y0 + rb meets A row rb - q for shift row q
-    const Words<RW + 1> wv = *reinterpret_cast<const Words<RW + 1>*>(Bb + (int64_t)rb * bpitch);
+    const Words<RW + 1> wv = bring[rb % PF];
+    if (rb + PF < 12) aring[(rb + PF) % (G + PF)] = arow(rb + PF);
+    if (rb + PF < 12 + 2 * R) bring[rb % PF] = brow(rb + PF);
     uint32_t rw[RW];
 #pragma unroll
     for (int i = 0; i < RW; ++i) rw[i] = __builtin_amdgcn_alignbyte(wv.w[i + 1], wv.w[i], sh);
@@ -768,7 +794,7 @@ __global__ __launch_bounds__(256) void k_sad_cells16_fine(SadArgs g) {
         if (r < 0 || r >= 12) continue;
         uint32_t sacc = acc[q][c];
 #pragma unroll
-        for (int i = 0; i < CWD; ++i) sacc = __builtin_amdgcn_sad_u16(aring[r % G].w[i], bw[i], sacc);
+        for (int i = 0; i < CWD; ++i) sacc = __builtin_amdgcn_sad_u16(aring[r % (G + PF)].w[i], bw[i], sacc);
         acc[q][c] = sacc;
       }
     }
@@ -1987,11 +2013,11 @@ hipError_t launch_sad_level(const Plan& P, int l, const void* A, const void* B, 
     dim3 grid(tiles, 1, n);
 #define PIV_SAD8(R_, D_) hipLaunchKernelGGL((k_sad_cells<R_, D_>), grid, dim3(64 * sad_passes<R_, D_>()), 0, s, g)
     switch (g.R) {
-      case 3: PIV_SAD8(3, 7); break;
-      case 4: PIV_SAD8(4, 5); break;
-      case 5: PIV_SAD8(5, 6); break;
-      case 6: PIV_SAD8(6, 7); break;
-      default: PIV_SAD8(7, 5); break;
+      case 3: PIV_SAD8(3, 4); break;
+      case 4: PIV_SAD8(4, 3); break;
+      case 5: PIV_SAD8(5, 4); break;
+      case 6: PIV_SAD8(6, 4); break;
+      default: PIV_SAD8(7, 4); break;
     }
 #undef PIV_SAD8
     return hipGetLastError();
@@ -2106,11 +2132,11 @@ hipError_t launch_sad_cost_cells(const Plan& P, uint32_t* C, int64_t cstride, in
 #define PIV_SADC(R_, D_) \
   hipLaunchKernelGGL((k_sad_cells<R_, D_, true>), grid, dim3(64 * sad_passes<R_, D_>()), 0, s, g)
   switch (g.R) {
-    case 3: PIV_SADC(3, 7); break;
-    case 4: PIV_SADC(4, 5); break;
-    case 5: PIV_SADC(5, 6); break;
-    case 6: PIV_SADC(6, 7); break;
-    default: PIV_SADC(7, 5); break;
+    case 3: PIV_SADC(3, 4); break;
+    case 4: PIV_SADC(4, 3); break;
+    case 5: PIV_SADC(5, 4); break;
+    case 6: PIV_SADC(6, 4); break;
+    default: PIV_SADC(7, 4); break;
   }
 #undef PIV_SADC
   return hipGetLastError();
