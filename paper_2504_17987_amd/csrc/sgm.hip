@@ -7,6 +7,8 @@
 // the key (cost, |dx|+|dy|, dy, dx).  Integer arithmetic throughout, so the
 // result is exact.  The level field it writes is read by the finer levels'
 // block matching exactly as a block-matched coarsest level is.
+#include <type_traits>
+
 #include "dev_common.h"
 #include "piv_internal.h"
 
@@ -93,26 +95,30 @@ struct Cand {
   uint32_t code[kPer]; // tie code (|dx|+|dy|, dy, dx) of the winner search
 };
 
-// One path direction over one line of nodes by one wave.  The costs (and
-// the running sums) of the node two ahead are requested before a node is
-// worked, into two register sets used in turn, so the global reads overlap
-// more than one node's work.  The workgroup is the one wave: its LDS reads
-// and writes complete in program order, so the exchange of the previous
-// node's costs needs no barrier (and none that would wait for the requests
-// in flight).  kWrite: the path's costs are stored into S (the first of the
-// four passes), otherwise added; kWta (the last pass): the node's total is
-// final and its winner, the least (S, |dx|+|dy|, dy, dx), is written.
-template <int kPer, bool kWrite, bool kWta>
-__device__ void sgm_path(const SgmArgs& g, const Cand<kPer>& cd, const uint32_t* C, uint32_t* S, int len,
-                         int64_t nstride, bool reverse, uint32_t* prev, int32_t* out, int node0, int nodestep) {
-  const int t = threadIdx.x;
+// What is done with a path's costs at a node: stored into S (the node's
+// first path), added to S, or added as the node's last path, whose total is
+// final: its winner, the least (S, |dx|+|dy|, dy, dx), is written.
+enum { kWrite, kAdd, kWta };
+
+// The nodes s0 .. s1 - 1 of a line, in the path's order, by one wave.  The
+// costs (and the running sums) of the node two ahead are requested before a
+// node is worked, into two register sets used in turn, so the global reads
+// overlap more than one node's work.  The wave's LDS reads and writes
+// complete in program order, so the exchange of the previous node's costs
+// needs no barrier (and none that would wait for the requests in flight).
+template <int kPer, int kMode>
+__device__ __forceinline__ void sgm_nodes(const SgmArgs& g, const Cand<kPer>& cd, const uint32_t* C, uint32_t* S,
+                                          int len, int s0, int s1, int64_t nstride, bool reverse, uint32_t* prev,
+                                          int32_t* out, int node0, int nodestep) {
+  if (s0 >= s1) return;
+  const int t = threadIdx.x & 63;
   const int P = 2 * g.R + 3;
   const int np = g.nx * g.ny;
   // (unconditional reads, padding lanes from the node's first candidate and
   // nodes past the end from the last node, so that the requests in flight
   // need no branches; the values are masked where they are used)
   auto request = [&](int s, uint32_t (&c_)[kPer], uint32_t (&s_)[kPer]) __attribute__((always_inline)) {
-    const int sc = min(s, len - 1);
+    const int sc = min(s, s1 - 1);
     const int pos = reverse ? len - 1 - sc : sc;
     const uint32_t* c = C + pos * nstride;
     const uint32_t* sp = S + pos * nstride;
@@ -120,7 +126,7 @@ __device__ void sgm_path(const SgmArgs& g, const Cand<kPer>& cd, const uint32_t*
     for (int e = 0; e < kPer; ++e) {
       const int k = cd.ok[e] ? t + e * 64 : 0;
       c_[e] = c[k];
-      if constexpr (!kWrite) s_[e] = sp[k];
+      if constexpr (kMode != kWrite) s_[e] = sp[k];
     }
   };
   auto node = [&](int s, uint32_t (&cq)[kPer], uint32_t (&sq)[kPer]) __attribute__((always_inline)) {
@@ -130,7 +136,7 @@ __device__ void sgm_path(const SgmArgs& g, const Cand<kPer>& cd, const uint32_t*
 #pragma unroll
     for (int e = 0; e < kPer; ++e) {
       cv[e] = cd.ok[e] ? cq[e] : 0u;
-      sv[e] = kWrite ? 0u : sq[e];
+      sv[e] = kMode == kWrite ? 0u : sq[e];
     }
     request(s + 2, cq, sq);
     // (the first node takes its own costs; its reads of prev are unused)
@@ -152,8 +158,8 @@ __device__ void sgm_path(const SgmArgs& g, const Cand<kPer>& cd, const uint32_t*
 #pragma unroll
     for (int e = 0; e < kPer; ++e) {
       prev[cd.wr[e]] = cur[e];
-      const uint32_t tot = kWrite ? cur[e] : sv[e] + cur[e];
-      if constexpr (kWta) {
+      const uint32_t tot = kMode == kWrite ? cur[e] : sv[e] + cur[e];
+      if constexpr (kMode == kWta) {
         const uint32_t tv = cd.ok[e] ? tot : 0xffffffffu;
         code = tv < best ? cd.code[e] : (tv == best ? min(code, cd.code[e]) : code);
         best = min(best, tv);
@@ -161,7 +167,7 @@ __device__ void sgm_path(const SgmArgs& g, const Cand<kPer>& cd, const uint32_t*
         if (cd.ok[e]) sp[t + e * 64] = tot;
       }
     }
-    if constexpr (kWta) {
+    if constexpr (kMode == kWta) {
       // (the least total, then among the lanes holding it the least code)
       const uint32_t mt = wave_min_u32(best);
       const uint32_t c = wave_min_u32(best == mt ? code : 0xffffffffu);
@@ -174,29 +180,36 @@ __device__ void sgm_path(const SgmArgs& g, const Cand<kPer>& cd, const uint32_t*
     // (these writes are issued before the next node's reads)
     __builtin_amdgcn_wave_barrier();
   };
-  uint32_t c0[kPer], s0[kPer], c1[kPer], s1[kPer];
-  request(0, c0, s0);
-  request(1, c1, s1);
-  int s = 0;
-  for (; s + 1 < len; s += 2) {
-    node(s, c0, s0);
-    node(s + 1, c1, s1);
+  uint32_t ca[kPer], sa[kPer], cb[kPer], sb[kPer];
+  request(s0, ca, sa);
+  request(s0 + 1, cb, sb);
+  int s = s0;
+  for (; s + 1 < s1; s += 2) {
+    node(s, ca, sa);
+    node(s + 1, cb, sb);
   }
-  if (s < len) node(s, c0, s0);
-  // the pass's sums are complete (in memory and LDS) before the next pass
-  __syncthreads();
+  if (s < s1) node(s, ca, sa);
 }
 
-// One wave per line.  dir 0: a node row, left to right then right to left;
-// dir 1: a node column, top to bottom then bottom to top, the last pass
-// taking each node's winner.
+// Two waves per line, one for each direction: dir 0: a node row, left to right
+// and right to left; dir 1: a node column, top to bottom and bottom to top.
+// They meet in the middle: in the first half of its path a wave comes to a
+// node first (and stores or adds), in the second half the other wave has been
+// there (and it adds, or takes the node's winner).  The sums are integers, so
+// their order does not matter.  A path is a chain of dependent nodes, and one
+// pair is bound by its latency (the prediction of one pair of 1 MP, R 6, 63 us
+// instead of 84); 64 pairs take 45 us
+// a launch, bound by the cost volumes' traffic (221 MB), where both
+// directions in turn by one wave took 49.5.
 template <int kPer>
-__global__ __launch_bounds__(64) void k_sgm_aggregate(SgmArgs g, int dir) {
-  __shared__ uint32_t prev[kPrevWords];
+__global__ __launch_bounds__(128) void k_sgm_aggregate(SgmArgs g, int dir) {
+  __shared__ uint32_t s_prev[2][kPrevWords];
   const int pair = blockIdx.y;
   if (slot_off(g.mask, pair)) return;
   const int line = blockIdx.x;
-  const int t = threadIdx.x;
+  const int t = threadIdx.x & 63;
+  const bool reverse = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) != 0;
+  uint32_t* prev = s_prev[reverse ? 1 : 0];
   const int n1 = 2 * g.R + 1, P = n1 + 2;
   for (int i = t; i < P * P; i += 64) prev[i] = 0xffffffffu;
   Cand<kPer> cd;
@@ -215,16 +228,19 @@ __global__ __launch_bounds__(64) void k_sgm_aggregate(SgmArgs g, int dir) {
   const uint32_t* C = g.C + (int64_t)pair * g.cstride;
   uint32_t* S = g.S + (int64_t)pair * g.cstride;
   int32_t* out = g.out + (int64_t)pair * g.ostride;
-  if (dir == 0) {
-    const int64_t base = (int64_t)line * g.nx * g.nd;
-    sgm_path<kPer, true, false>(g, cd, C + base, S + base, g.nx, g.nd, false, prev, out, 0, 0);
-    sgm_path<kPer, false, false>(g, cd, C + base, S + base, g.nx, g.nd, true, prev, out, 0, 0);
-  } else {
-    const int64_t base = (int64_t)line * g.nd;
-    const int64_t ns = (int64_t)g.nx * g.nd;
-    sgm_path<kPer, false, false>(g, cd, C + base, S + base, g.ny, ns, false, prev, out, 0, 0);
-    sgm_path<kPer, false, true>(g, cd, C + base, S + base, g.ny, ns, true, prev, out, line, g.nx);
-  }
+  const int len = dir == 0 ? g.nx : g.ny;
+  const int64_t base = dir == 0 ? (int64_t)line * g.nx * g.nd : (int64_t)line * g.nd;
+  const int64_t ns = dir == 0 ? g.nd : (int64_t)g.nx * g.nd;
+  const int node0 = dir == 0 ? 0 : line, nodestep = dir == 0 ? 0 : g.nx;   // (the winner's, dir 1)
+  const int half = reverse ? len / 2 : (len + 1) / 2;
+  auto nodes = [&](auto mode, int s0, int s1) {
+    sgm_nodes<kPer, decltype(mode)::value>(g, cd, C + base, S + base, len, s0, s1, ns, reverse, prev, out, node0, nodestep);
+  };
+  if (dir == 0) nodes(std::integral_constant<int, kWrite>{}, 0, half);
+  else nodes(std::integral_constant<int, kAdd>{}, 0, half);
+  __syncthreads();   // both waves' sums of their first halves are in memory
+  if (dir == 0) nodes(std::integral_constant<int, kAdd>{}, half, len);
+  else nodes(std::integral_constant<int, kWta>{}, half, len);
 }
 
 }  // namespace
@@ -267,7 +283,7 @@ hipError_t launch_sgm_level(const Plan& P, int n, hipStream_t s) {
   for (int dir = 0; dir < 2; ++dir) {
     dim3 ga(dir == 0 ? v.ny : v.nx, n);
 #define PIV_SGM_AGG(K_) \
-  if (per <= K_) { hipLaunchKernelGGL(k_sgm_aggregate<K_>, ga, dim3(64), 0, s, g, dir); }
+  if (per <= K_) { hipLaunchKernelGGL(k_sgm_aggregate<K_>, ga, dim3(128), 0, s, g, dir); }
     PIV_SGM_AGG(1) else PIV_SGM_AGG(3) else PIV_SGM_AGG(4) else PIV_SGM_AGG(8) else PIV_SGM_AGG(12) else PIV_SGM_AGG(18)
 #undef PIV_SGM_AGG
     if (hipError_t e = hipGetLastError()) return e;
