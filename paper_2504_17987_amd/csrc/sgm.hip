@@ -197,10 +197,9 @@ __device__ __forceinline__ void sgm_nodes(const SgmArgs& g, const Cand<kPer>& cd
 // node first (and stores or adds), in the second half the other wave has been
 // there (and it adds, or takes the node's winner).  The sums are integers, so
 // their order does not matter.  A path is a chain of dependent nodes, and one
-// pair is bound by its latency (the prediction of one pair of 1 MP, R 6, 63 us
-// instead of 84); 64 pairs take 45 us
-// a launch, bound by the cost volumes' traffic (221 MB), where both
-// directions in turn by one wave took 49.5.
+// pair is bound by its latency (the prediction of one pair of 1 MP, R 6: 63 us
+// instead of 84); 64 pairs take 45 us a launch, bound by the cost volumes'
+// traffic (221 MB), where one wave taking both paths in turn took 49.5.
 template <int kPer>
 __global__ __launch_bounds__(128) void k_sgm_aggregate(SgmArgs g, int dir) {
   __shared__ uint32_t s_prev[2][kPrevWords];
