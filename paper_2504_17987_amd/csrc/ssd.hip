@@ -402,8 +402,8 @@ __device__ __forceinline__ void ssd_column(const SsdArgs& a, const SsdFrame& A, 
 // Forward: the squared residuals of every column of a strip are summed in its
 // thread, then 4 threads per window add a quarter of its 2 strips x 16
 // columns each.  Bound by the address rate of the vector caches (23 million
-// accesses, some 16 a gather, or 38 us at one a cycle and CU; 46 VALU
-// operations a pixel are 25 us): 64 pairs of 512 x 512 38 us (57 us with a
+// accesses, some 16 a gather, or 38 us at one a cycle and CU; 41 VALU
+// operations a pixel are 22 us): 64 pairs of 512 x 512 38 us (57 us with a
 // thread per pixel, which weighed its four nodes by itself and read the
 // cell's corners one by one).
 __global__ __launch_bounds__(256, 6) void k_ssd_forward_t(SsdArgs a) {
@@ -484,8 +484,8 @@ __device__ __forceinline__ float tile_sum(float x, float* red) {
 // constant along it); pass 2 sums a node's partials over its columns with
 // the column weights.  The displacement is interpolated down the two node
 // columns and then across, the order that decides in which cell a sample at a
-// cell's edge falls.  Bound by VALU issue, some 50 operations a pixel and 80
-// at the frames' border: 64 pairs of 512 x 512 50 us (99 us with a thread per
+// cell's edge falls.  Bound by VALU issue (0.92 of it; 88 operations a
+// pixel with the node sums, half again as many at the frames' border): 64 pairs of 512 x 512 50 us (99 us with a thread per
 // eight pixels of a row, whose gathers touched a cache line per lane and whose
 // node sums read every row's partials).
 constexpr int kPartPlane = kCols + 1;               // odd: the terms' planes on different banks,
