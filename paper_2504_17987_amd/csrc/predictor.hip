@@ -838,22 +838,28 @@ __global__ __launch_bounds__(256) void k_sad_cells16_fine(SadArgs g) {
 // centre, the addressing and the winner search are paid once per three
 // cells.  Level 0 reads in place as in k_sad_lane.  Winner: the least 31-bit
 // key as in k_sad_lane.
+// kSplit, for few tiles: a workgroup per tile whose waves take a shift row
+// each (their chains are a fifth as long) and whose first wave merges their
+// winners by the key.
 // ---------------------------------------------------------------------------
-template <int R>
-__global__ __launch_bounds__(256) void k_sad_cols(SadArgs g) {
+template <int R, bool kSplit>
+__global__ __launch_bounds__(kSplit ? 64 * (2 * R + 1) : 256) void k_sad_cols(SadArgs g) {
   constexpr int G = 2 * R + 1, NGRP = (G + 3) / 4, REM = G - 4 * (NGRP - 1);
   constexpr bool TAIL = REM <= 2;
   constexpr int NQ = TAIL ? NGRP - 1 : NGRP;
   constexpr int CWD = 2, RW = CWD + NGRP, PPW = 21;   // parents per wave
   constexpr int NA = 24, NB = NA + G - 1;             // A and B rows of the column
+  constexpr int QPW = kSplit ? 1 : G;                 // shift rows per wave
   static_assert(G <= 5, "one pass of shift rows");
   const int lane = threadIdx.x & 63;
   const WgIdx wg = xcd_order();
   const int pair = wg.z;
   if (slot_off(g.mask, pair)) return;
   const int pnx = (g.nx + 1) / 2, pny = (g.ny + 1) / 2;
-  const int p0 = (wg.x * 4 + (threadIdx.x >> 6)) * PPW;   // the wave's first parent, counted along the rows
-  if (p0 >= pnx * pny) return;   // a whole wave (no barriers below)
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q0 = kSplit ? wave : 0;                   // the wave's first shift row
+  const int p0 = (kSplit ? wg.x : wg.x * 4 + wave) * PPW;   // the wave's first parent, counted along the rows
+  if (p0 >= pnx * pny) return;   // a whole wave, and with kSplit the workgroup
   const int grp = min(lane / 3, PPW - 1), v = lane - 3 * (lane / 3);
   const int p = min(p0 + grp, pnx * pny - 1);
   const int pa = p / pnx, pb = p - pa * pnx;
@@ -876,7 +882,7 @@ __global__ __launch_bounds__(256) void k_sad_cols(SadArgs g) {
   const unsigned pa32 = ain ? spitch32 : pitch32, pb32 = bin ? spitch32 : pitch32;
   const int am = ain ? 0 : g.margin, bm = bin ? 0 : g.margin;
   const unsigned aoff = __umul24((unsigned)(y + am), pa32) + (unsigned)(x + am);
-  const unsigned boff = __umul24((unsigned)(y0 + bm), pb32) + (unsigned)(xa + bm);
+  const unsigned boff = __umul24((unsigned)(y0 + q0 + bm), pb32) + (unsigned)(xa + bm);
   auto arow = [&](int r) {
     const unsigned o = aoff + r * pa32;
     return ain ? *reinterpret_cast<const Words<CWD>*>(Asrc + (size_t)o)
@@ -887,39 +893,39 @@ __global__ __launch_bounds__(256) void k_sad_cols(SadArgs g) {
     return bin ? *reinterpret_cast<const Words<RW + 1>*>(Bsrc + (size_t)o)
                : *reinterpret_cast<const Words<RW + 1>*>(Bpad + (size_t)o);
   };
-  unsigned long long acc[3][G][NQ > 0 ? NQ : 1];
-  uint32_t tacc[3][G][2];
+  unsigned long long acc[3][QPW][NQ > 0 ? NQ : 1];
+  uint32_t tacc[3][QPW][2];
 #pragma unroll
   for (int u = 0; u < 3; ++u)
 #pragma unroll
-    for (int q = 0; q < G; ++q) {
+    for (int q = 0; q < QPW; ++q) {
 #pragma unroll
       for (int m = 0; m < (NQ > 0 ? NQ : 1); ++m) acc[u][q][m] = 0ull;
       tacc[u][q][0] = tacc[u][q][1] = 0u;
     }
-  constexpr int PF = 4;   // B and A rows read PF rows ahead of their use
+  constexpr int PF = kSplit ? 8 : 4;   // B and A rows read PF rows ahead of their use
   Words<RW + 1> bring[PF];
-  Words<CWD> aring[G + PF];
+  Words<CWD> aring[QPW + PF];
 #pragma unroll
   for (int i = 0; i < PF; ++i) {
     bring[i] = brow(i);
     aring[i] = arow(i);
   }
 #pragma unroll
-  for (int rb = 0; rb < NB; ++rb) {
-    // B row y0 + rb meets A row rb - q (cell (rb - q) / 8) for shift row q
+  for (int rb = 0; rb < NA + QPW - 1; ++rb) {
+    // B row y0 + q0 + rb meets A row rb - q (cell (rb - q) / 8) for shift row q0 + q
     const Words<RW + 1> wv = bring[rb % PF];
-    if (rb + PF < NB) bring[rb % PF] = brow(rb + PF);
-    if (rb + PF < NA) aring[(rb + PF) % (G + PF)] = arow(rb + PF);
+    if (rb + PF < NA + QPW - 1) bring[rb % PF] = brow(rb + PF);
+    if (rb + PF < NA) aring[(rb + PF) % (QPW + PF)] = arow(rb + PF);
     uint32_t rw[RW];
 #pragma unroll
     for (int i = 0; i < RW; ++i) rw[i] = __builtin_amdgcn_alignbyte(wv.w[i + 1], wv.w[i], sh);
 #pragma unroll
-    for (int q = 0; q < G; ++q) {
+    for (int q = 0; q < QPW; ++q) {
       const int r = rb - q;
       if (r < 0 || r >= NA) continue;
       const int u = r / 8;
-      const Words<CWD> aw = aring[r % (G + PF)];
+      const Words<CWD> aw = aring[r % (QPW + PF)];
 #pragma unroll
       for (int i = 0; i < CWD; ++i) {
 #pragma unroll
@@ -942,17 +948,16 @@ __global__ __launch_bounds__(256) void k_sad_cols(SadArgs g) {
   auto pair_sum = [&](uint32_t val) {
     return val + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)val, 0x130, 0xF, 0xF, false);
   };
-  uint32_t kx[G], ky[G];
+  uint32_t kx[G], ky[QPW];
 #pragma unroll
-  for (int k = 0; k < G; ++k) {
-    kx[k] = ((uint32_t)abs(cx - R + k) << 6) | (uint32_t)k;
-    ky[k] = ((uint32_t)abs(cy - R + k) << 6) | ((uint32_t)k << 3);
-  }
+  for (int k = 0; k < G; ++k) kx[k] = ((uint32_t)abs(cx - R + k) << 6) | (uint32_t)k;
+#pragma unroll
+  for (int k = 0; k < QPW; ++k) ky[k] = ((uint32_t)abs(cy - R + q0 + k) << 6) | ((uint32_t)(q0 + k) << 3);
   uint32_t best[2] = {~0u, ~0u};
 #pragma unroll
   for (int uc = 0; uc < 2; ++uc) {
 #pragma unroll
-    for (int q = 0; q < G; ++q) {
+    for (int q = 0; q < QPW; ++q) {
 #pragma unroll
       for (int m = 0; m < NQ; ++m) {
         const unsigned long long t2 = acc[uc][q][m] + acc[uc + 1][q][m];   // fields stay below 2^15
@@ -974,6 +979,18 @@ __global__ __launch_bounds__(256) void k_sad_cols(SadArgs g) {
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+  }
+  if constexpr (kSplit) {
+    // the waves' winners: the least key over the shift rows
+    __shared__ uint32_t s_best[G][2][64];
+    s_best[wave][0][lane] = best[0];
+    s_best[wave][1][lane] = best[1];
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int q = 1; q < G; ++q)
+#pragma unroll
+      for (int uc = 0; uc < 2; ++uc) best[uc] = min(best[uc], s_best[q][uc][lane]);
   }
   const int b = 2 * pb + v;
   const bool col = lane < 3 * PPW && v < 2 && p0 + lane / 3 < pnx * pny && b < g.nx;
@@ -1970,9 +1987,18 @@ hipError_t launch_sad_level(const Plan& P, int l, const void* A, const void* B, 
   if (g.parent && P.es == 1 && P.p.step == 8 && P.block == 16 && g.R >= 1 && g.R <= 2 &&
       (size_t)v.rows * v.pitch < (1u << 31) && v.pitch < (1 << 24)) {
     const int tiles3 = (((v.nx + 1) / 2) * ((v.ny + 1) / 2) + 20) / 21;
-    const dim3 grid3((tiles3 + 3) / 4, 1, n);
-    if (g.R == 2) hipLaunchKernelGGL((k_sad_cols<2>), grid3, dim3(256), 0, s, g);
-    else hipLaunchKernelGGL((k_sad_cols<1>), grid3, dim3(256), 0, s, g);
+    // a shift row per wave where that many waves leave the chip no fuller:
+    // one pair of 1 MP (49 and 196 tiles a level) 6.4 us a level instead of
+    // 7.2; 392 tiles 20.9 us a prediction instead of 19.9
+    const bool split = (int64_t)tiles3 * n <= 256;
+    const dim3 grid3(split ? tiles3 : (tiles3 + 3) / 4, 1, n);
+    if (g.R == 2) {
+      if (split) hipLaunchKernelGGL((k_sad_cols<2, true>), grid3, dim3(320), 0, s, g);
+      else hipLaunchKernelGGL((k_sad_cols<2, false>), grid3, dim3(256), 0, s, g);
+    } else {
+      if (split) hipLaunchKernelGGL((k_sad_cols<1, true>), grid3, dim3(192), 0, s, g);
+      else hipLaunchKernelGGL((k_sad_cols<1, false>), grid3, dim3(256), 0, s, g);
+    }
     return hipGetLastError();
   }
   const bool off31 = (size_t)v.rows * v.pitch < (1u << 31) && v.pitch < (1 << 24);

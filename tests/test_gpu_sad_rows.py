@@ -13,6 +13,7 @@ pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a HIP device")]
 
 # dtype, grid, levels, radius_coarse, radius_fine
+# (few tiles: a workgroup per 21 parents; 20 pairs: a wave)
 CASES = [("u8", g, 2, rc, rf) for g in ((43, 27), (85, 3), (3, 44), (22, 21), (42, 42)) for rc, rf in ((3, 1), (6, 2))] + \
         [("u8", (19, 14), 1, rc, 2) for rc in (3, 4, 5, 6, 7)] + \
         [("u16", g, 2, 3, rf) for g in ((29, 15), (14, 3), (3, 29)) for rf in (1, 2)]
@@ -39,3 +40,18 @@ def test_predict_parents_over_row_ends(dtype, grid, levels, rc, rf):
     for i, (a, b) in enumerate(prs):
         ref = oracle.predict(a, b, step, 2 * step, levels, rc, rf).astype(np.float32)
         assert np.array_equal(got[i], ref), (i, np.argwhere(got[i] != ref)[:4])
+
+
+@pytest.mark.parametrize("rf", [1, 2])
+def test_predict_many_pairs_as_few(rf):
+    from paper_2504_17987_amd import api
+    W, H, n = 8 * 43, 8 * 27, 20
+    rng = np.random.default_rng(rf)
+    A = rng.integers(0, 256, (2, H, W), dtype=np.uint8)
+    B = np.where(rng.random((2, H, W)) < 0.3, rng.integers(0, 256, (2, H, W), dtype=np.uint8), np.roll(A, (3, -5), (1, 2)))
+    ref = [oracle.predict(A[i], B[i], 8, 16, 2, 6, rf).astype(np.float32) for i in range(2)]
+    P = api.Plan(W, H, max_batch=n, levels=2, radius_coarse=6, radius_fine=rf)
+    rep = lambda x: torch.from_numpy(np.ascontiguousarray(np.tile(x, (n // 2, 1, 1)))).cuda()  # noqa: E731
+    got = P.predict(rep(A), rep(B)).cpu().numpy()
+    for i in range(n):
+        assert np.array_equal(got[i], ref[i % 2]), i
