@@ -17,11 +17,12 @@
 //    shared by the four windows that contain the cell; window sums are then
 //    assembled from cell sums.
 //
-// Numerics (FP32): all sums are taken about a per-tile integer offset K
-// (the rounded mean intensity of the tile), which leaves the coefficient
-// unchanged and keeps E[x^2] - E[x]^2 well conditioned.  A window counts as
-// flat when its variance is below 1e-6 of its second moment about K (an
-// exact zero cannot be certified in FP32); a flat window has coefficient 0.
+// Numerics (FP32): all sums are taken about an integer offset K (the rounded
+// mean intensity of the tile; of the window in k_correct_generic and
+// k_correct_rows), which leaves the coefficient unchanged and keeps
+// E[x^2] - E[x]^2 well conditioned.  A window counts as flat when its
+// variance is below 1e-6 of its second moment about K (an exact zero cannot
+// be certified in FP32); a flat window has coefficient 0.
 #include <type_traits>
 
 #include "dev_common.h"
@@ -2249,14 +2250,26 @@ void k_correct_halves(CorrArgs g) {
 // and a tile of 63 cells more than a small frame has, so here a thread takes
 // one cell, one row of shifts and one of PARTS interleaved parts of the
 // cell's rows: it streams those rows of A and B' from LDS and keeps 2R+1
-// sums of products.  PARTS neighbouring lanes add up by DPP, the cells' sums
-// meet in LDS, and a thread per (window, shift row) forms the coefficients.
-// The box sums S and Q of B' are taken per window, columns first (a thread
-// per column and window row), then along the row: sums over the rows
-// (columns) that every shift shares, plus running sums at both ends, so that
-// nothing is subtracted.  Frames are deformed by the whole predictor (B
-// only), or by half of it each (kCentral; A' is then held as floats, else
-// the packed pixels are).
+// sums of products, which PARTS neighbouring lanes add up by DPP.  The box
+// sums S and Q of B' and its square are taken per cell, columns first (a
+// thread per column and cell row), then along the row (a thread per cell,
+// shift row and sum): sums over the rows (columns) that every shift shares,
+// plus running sums at both ends, so that nothing is subtracted.  The cells'
+// sums meet in LDS, where threads per window, shift row and a few columns
+// form the coefficients.
+// A cell's sums are taken about its own mean Kc, and a window's from its four
+// cells' about the window's mean Kw: with d = Kc - Kw, n the pixels of a cell
+// and P, S, s its sums of (A-Kc)(B'-Kc), B'-Kc and A-Kc,
+//   sum (A-Kw)(B'-Kw) = sum over cells of P + d (S + s + n d),
+// so light that differs from window to window costs no bits: 12-bit frames
+// with particles of 300 under light of 3000 +- 600, error of the coefficient
+// 0.8e-6 at most, as about each window's mean by itself; about the mean of a
+// tile of windows, and with A as it is, 42e-6.  4 x 1024 x 512 u8 frames, r 4:
+// 37.5 us, 22.6 of VALU issue and 20 of LDS reads side by side (34.3 us about
+// the tile's mean; k_correct_generic 454); one 256 x 256 pair, r 8: 14.2 us
+// (generic 36).
+// Frames are deformed by the whole predictor (B only), or by half of it each
+// (kCentral; A' is then held as floats, else the packed pixels are).
 // ---------------------------------------------------------------------------
 template <typename T, int STEP, int R, int TW, int TH, int PARTS, int NT, bool kCentral>
 struct RowsCfg {
@@ -2270,19 +2283,22 @@ struct RowsCfg {
   static constexpr int AP = kCentral ? odd4(AW) : AW * ES / 4;           // words
   static constexpr int NNX = BW / STEP + 4, NNY = BH / STEP + 3;         // predictor nodes of the B' tile
   static constexpr int BRW = STEP + 2 * R;                               // B' columns of one cell
-  static constexpr int WRW = WIN + 2 * R;                                // B' columns of one window
-  static constexpr int PP = (NSY + 3) / 4 * 4;                           // sums of one item, padded
   static constexpr int NI = NC * NSY * PARTS;                            // items (threads) of the products
   // raw source box: the tile plus a predictor range of 17 px across it
   static constexpr int RAW = (BH + 20) * (((BW + 20) * ES + 3) / 4 + 2);
-  static constexpr int VS = TH * NSY * BP, PW = NC * NSY * PP;
-  // [raw box, then the column sums S and Q] [A] [B', then the cells' sums]
+  // [raw box, then the column sums S and Q] [A] [B'], then the cells' sums
+  // P, S, Q: [3][cell][shift row][shift column], and behind them the
+  // coefficients [window][shift]
+  static constexpr int VS = CH * NSY * BP, RES = 3 * NC * NSY * NSY;
   static constexpr int AWORDS = AH * AP;
   static constexpr int RV = kCentral ? (2 * VS > RAW + AWORDS ? 2 * VS - AWORDS : RAW) : (2 * VS > RAW ? 2 * VS : RAW);
-  static constexpr int BWORDS = BH * BP > PW ? BH * BP : PW;
-  static constexpr int TOTAL = (RV + 3) / 4 * 4 + AWORDS + BWORDS;
+  static constexpr int IN = (RV + 3) / 4 * 4 + AWORDS + BH * BP;
+  static constexpr int OUT = RES + NWIN * NSY * NSY;
+  static constexpr int TOTAL = IN > OUT ? IN : OUT;
   static_assert(NI <= NT, "one item per thread");
-  static_assert(NWIN * NSY <= NT, "a thread per window and shift row");
+  static_assert(2 * NC * NSY <= NT, "a thread per cell, shift row and sum");
+  // shift columns a thread turns into coefficients: as few as the threads allow
+  static constexpr int JG = []() { int j = 1; while (NWIN * NSY * ((NSY + j - 1) / j) > NT) ++j; return j; }();
   static_assert(STEP == 16 && STEP % PARTS == 0 && (PARTS & (PARTS - 1)) == 0 && PARTS <= 16, "parts add up by DPP");
 };
 
@@ -2291,19 +2307,21 @@ __global__ __launch_bounds__(NT) void k_correct_rows(CorrArgs g) {
   using C = RowsCfg<T, STEP, R, TW, TH, PARTS, NT, kCentral>;
   constexpr int ES = C::ES, NSY = C::NSY;
   __shared__ __align__(16) float s_mem[C::TOTAL];
-  __shared__ float s_rho[C::NWIN * NSY * NSY];
-  __shared__ float s_best[C::NWIN * NSY];
-  __shared__ int s_key[C::NWIN * NSY];   // tie key << 1 | every used shift of the row flat
+  // per window: d of its cells, mean and variance of A - Kw, and what d adds
+  // to P, S and Q by itself
+  __shared__ __align__(16) float s_win[C::NWIN][12];
+  __shared__ int s_sharp[C::NWIN];       // a used shift that is not flat
   __shared__ float s_node[2][C::NNY][C::NNX];
   __shared__ int s_rb[C::BH], s_cb[(C::BW + 3) / 4 * 4];
   __shared__ float s_rf[C::BH], s_cf[(C::BW + 3) / 4 * 4];
-  __shared__ float s_ca[2][C::NC];       // per cell: sum of A - K and of its square
-  __shared__ float s_red[(NT + 63) / 64];
+  __shared__ float s_cell[3][C::NC];     // per cell: Kc, sum of A - Kc and of its square
+  __shared__ float s_red[NT / 64];
   float* const sV = s_mem;
   uint32_t* const sraw = reinterpret_cast<uint32_t*>(s_mem);
   float* const sA = s_mem + (C::RV + 3) / 4 * 4;
   uint32_t* const sAw = reinterpret_cast<uint32_t*>(sA);
   float* const sB = sA + C::AWORDS;
+  float* const s_rho = s_mem + C::RES;
 
   const WgIdx wg = xcd_order();
   const int pair = wg.z;
@@ -2441,12 +2459,14 @@ __global__ __launch_bounds__(NT) void k_correct_rows(CorrArgs g) {
     return b;
   };
   // deformed tile rows x cols4 (whole groups of four columns) at (ty, tx),
-  // table rows / columns from (tr, tc), minus K, into dst
+  // table rows / columns from (tr, tc), minus K, into dst; returns the
+  // thread's sum
   auto deform = [&](const uint8_t* img, const Box& b, int ty, int tx, int rows, int cols4, int tr, int tc, float s,
-                    float K, float* dst, int pitch, float& sum, auto uniform) __attribute__((always_inline)) {
+                    float K, float* dst, int pitch, auto uniform) __attribute__((always_inline)) {
     // uniform: no group of four straddles a node column
     constexpr bool kUni = decltype(uniform)::value;
     const int nq = cols4 / 4;
+    float sum = 0.0f;
     const uint8_t* rawb = reinterpret_cast<const uint8_t*>(sraw);
     const int rowb = 4 * b.nwords, xadd = b.ix0 * ES - 4 * ((b.ix0 * ES) >> 2);
     const unsigned ixhi = (unsigned)(b.ix1 - 1 - b.ix0), iyhi = (unsigned)(b.iy1 - 1 - b.iy0);
@@ -2512,12 +2532,13 @@ __global__ __launch_bounds__(NT) void k_correct_rows(CorrArgs g) {
       sum += (out[0] + out[1]) + (out[2] + out[3]);
       *reinterpret_cast<float4*>(dst + r * pitch + q) = make_float4(out[0], out[1], out[2], out[3]);
     }
+    return sum;
   };
 
   if constexpr (kCentral) {
     const Box ab = stage(Ai, y0, x0, C::AH, C::AW, -0.5f);
     __syncthreads();
-    deform(Ai, ab, y0, x0, C::AH, C::AW, R, R, -0.5f, 0.0f, sA, C::AP, asum, std::true_type());
+    asum = deform(Ai, ab, y0, x0, C::AH, C::AW, R, R, -0.5f, 0.0f, sA, C::AP, std::true_type());
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) asum += __shfl_xor(asum, o);
     __syncthreads();   // the raw box of A is read
@@ -2525,15 +2546,13 @@ __global__ __launch_bounds__(NT) void k_correct_rows(CorrArgs g) {
   if (lane == 0) s_red[t >> 6] = asum;
   const Box bb = stage(Bi, yb, xb, C::BH, C::BW, kCentral ? 0.5f : 1.0f);
   __syncthreads();
-  // the tile offset K: the rounded mean of the A tile
+  // K, the rounded mean of the A tile: what B' is held about
   float K = 0.0f;
 #pragma unroll
-  for (int i = 0; i < (NT + 63) / 64; ++i) K += s_red[i];
+  for (int i = 0; i < NT / 64; ++i) K += s_red[i];
   K = rintf(K / (float)(C::AH * C::AW));
-  float unused = 0.0f;
-  deform(Bi, bb, yb, xb, C::BH, BW4, 0, 0, kCentral ? 0.5f : 1.0f, K, sB, C::BP, unused,
+  deform(Bi, bb, yb, xb, C::BH, BW4, 0, 0, kCentral ? 0.5f : 1.0f, K, sB, C::BP,
          std::bool_constant<(STEP + R) % 4 == 0>());
-  __syncthreads();
 
   // pixel x of a cell row of A
   auto arow = [&](int cy, int cx, int py, float (&ar)[STEP]) __attribute__((always_inline)) {
@@ -2565,23 +2584,55 @@ __global__ __launch_bounds__(NT) void k_correct_rows(CorrArgs g) {
     if (n > 8) v += dpp(v, std::integral_constant<int, 0x140>());
     return v;
   };
-  // ---- products: P = sum A (B' - K) over the thread's rows of its cell
+  // ---- per cell: Kc, the rounded mean of A, the sum of A - Kc and of its
+  // square, a lane per cell row
+  constexpr float kInvCell = 1.0f / (float)(STEP * STEP);
+  for (int i = t; i < (16 * C::NC + 63) / 64 * 64; i += NT) {
+    const int c = min(i >> 4, C::NC - 1), py = i & 15;
+    float ar[STEP], s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
+    arow(c / C::CW, c - (c / C::CW) * C::CW, py, ar);
+#pragma unroll
+    for (int x = 0; x < STEP; ++x) s0 += ar[x];
+    const float Kc = rintf(lanes_sum(s0, 16) * kInvCell);
+#pragma unroll
+    for (int x = 0; x < STEP; ++x) {
+      const float d = ar[x] - Kc;
+      s1 += d;
+      s2 += d * d;
+    }
+    s1 = lanes_sum(s1, 16);
+    s2 = lanes_sum(s2, 16);
+    if (py == 0) {
+      s_cell[0][c] = Kc;
+      s_cell[1][c] = s1;
+      s_cell[2][c] = s2;
+    }
+  }
+  __syncthreads();
+  // ---- products: P = sum (A - Kc)(B' - Kc) over the thread's rows of its cell
   const int q = t / PARTS, part = t - q * PARTS;
   const int sy_i = q % NSY, cell = q / NSY;
   float P[NSY];
   if (t < C::NI) {
     const int ci = cell / C::CW, cj = cell - (cell / C::CW) * C::CW;
+    const float Kc = s_cell[0][cell], kb = Kc - K;
 #pragma unroll
     for (int j = 0; j < NSY; ++j) P[j] = 0.0f;
     const float* bbase = sB + (ci * STEP + sy_i) * C::BP + cj * STEP;
-    // one row at a time in flight beside the one worked on
-#pragma unroll 2
+    // one row at a time in flight beside the one worked on (r 8: its rows do
+    // not fit the registers of four waves a SIMD)
+    constexpr int kRows = R > 4 ? 1 : 2;
+#pragma unroll kRows
     for (int k = 0; k < STEP / PARTS; ++k) {
       const int py = part + PARTS * k;
       float ar[STEP], br[C::BRW];
       arow(ci, cj, py, ar);
 #pragma unroll
       for (int x = 0; x < C::BRW; ++x) br[x] = bbase[py * C::BP + x];
+#pragma unroll
+      for (int x = 0; x < STEP; ++x) ar[x] -= Kc;
+#pragma unroll
+      for (int x = 0; x < C::BRW; ++x) br[x] -= kb;
 #pragma unroll
       for (int x = 0; x < STEP; ++x)
 #pragma unroll
@@ -2590,152 +2641,207 @@ __global__ __launch_bounds__(NT) void k_correct_rows(CorrArgs g) {
 #pragma unroll
     for (int j = 0; j < NSY; ++j) P[j] = lanes_sum(P[j], PARTS);
   }
-  // ---- per cell: sum of A - K and of its square, a lane per cell row
-  for (int i = t; i < (16 * C::NC + 63) / 64 * 64; i += NT) {
-    const int c = min(i >> 4, C::NC - 1), py = i & 15;
-    float ar[STEP], s1 = 0.0f, s2 = 0.0f;
-    arow(c / C::CW, c - (c / C::CW) * C::CW, py, ar);
-#pragma unroll
-    for (int x = 0; x < STEP; ++x) {
-      const float d = ar[x] - K;
-      s1 += d;
-      s2 += d * d;
-    }
-    s1 = lanes_sum(s1, 16);
-    s2 = lanes_sum(s2, 16);
-    if (py == 0) {
-      s_ca[0][c] = s1;
-      s_ca[1][c] = s2;
-    }
-  }
   if constexpr (kCentral) __syncthreads();   // A' is read: the column sums take its place
-  // ---- column sums of B' over every window row and row shift
-  for (int i = t; i < TH * C::BW; i += NT) {
-    const int wi = i / C::BW, x = i - (i / C::BW) * C::BW;
-    const float* col = sB + wi * STEP * C::BP + x;
-    float* vs = sV + wi * NSY * C::BP + x;
+  // ---- column sums of B' and its square over every cell row and row shift,
+  // about the mean of the cell whose columns they are
+  auto cell_of = [&](int ci, int x) { return ci * C::CW + min(max((x - R) >> 4, 0), C::CW - 1); };
+  for (int i = t; i < C::CH * C::BW; i += NT) {
+    const int ci = i / C::BW, x = i - (i / C::BW) * C::BW;
+    const float* col = sB + ci * STEP * C::BP + x;
+    float* vs = sV + ci * NSY * C::BP + x;
     float* vq = vs + C::VS;
-    float head[2 * R], s = 0.0f, q2 = 0.0f;
+    const float kb = s_cell[0][cell_of(ci, x)] - K;
+    float v[STEP + 2 * R];
 #pragma unroll
-    for (int r = 0; r < 2 * R; ++r) head[r] = col[r * C::BP];
-#pragma unroll 8
-    for (int r = 2 * R; r < C::WIN; ++r) {
-      const float v = col[r * C::BP];
-      s += v;
-      q2 += v * v;
+    for (int r = 0; r < STEP + 2 * R; ++r) v[r] = col[r * C::BP] - kb;
+    float s = 0.0f, q2 = 0.0f;
+#pragma unroll
+    for (int r = 2 * R; r < STEP; ++r) {
+      s += v[r];
+      q2 += v[r] * v[r];
     }
     // rows the shift takes from the head, last row first, then the tail's
     float hs[NSY], hq[NSY];
     hs[2 * R] = hq[2 * R] = 0.0f;
 #pragma unroll
     for (int r = 2 * R - 1; r >= 0; --r) {
-      hs[r] = hs[r + 1] + head[r];
-      hq[r] = hq[r + 1] + head[r] * head[r];
+      hs[r] = hs[r + 1] + v[r];
+      hq[r] = hq[r + 1] + v[r] * v[r];
     }
     float ts = 0.0f, tq = 0.0f;
 #pragma unroll
     for (int k = 0; k < NSY; ++k) {
       if (k > 0) {
-        const float v = col[(C::WIN + k - 1) * C::BP];
-        ts += v;
-        tq += v * v;
+        ts += v[STEP + k - 1];
+        tq += v[STEP + k - 1] * v[STEP + k - 1];
       }
       vs[k * C::BP] = hs[k] + s + ts;
       vq[k * C::BP] = hq[k] + q2 + tq;
     }
   }
-  __syncthreads();   // B' is read: the cells' sums take its place
-  if (t < C::NI && part == 0) {
-    float* o = sB + (sy_i * C::NC + cell) * C::PP;
-#pragma unroll
-    for (int j = 0; j < NSY; ++j) o[j] = P[j];
-  }
   __syncthreads();
-  // ---- a thread per (window, shift row): coefficients and the row's peak
-  if (t < C::NWIN * NSY) {
-    const int w = t / NSY, k = t - w * NSY, sy = k - R;
-    const int wi = w / TW, wj = w - (w / TW) * TW;
-    constexpr float kInvN = 1.0f / (float)(C::WIN * C::WIN);
-    const int c00 = wi * C::CW + wj, c10 = c00 + C::CW;
-    const float sa = (s_ca[0][c00] + s_ca[0][c00 + 1]) + (s_ca[0][c10] + s_ca[0][c10 + 1]);
-    const float saa = (s_ca[1][c00] + s_ca[1][c00 + 1]) + (s_ca[1][c10] + s_ca[1][c10 + 1]);
-    const float mA = sa * kInvN, varA = saa - sa * mA, meanA = K + mA;
-    const bool flatA = !(varA > kFlatRel * saa);
-    // box sums along the row of column sums
-    float S[NSY], Q[NSY];
-    auto boxes = [&](const float* p, float (&o)[NSY]) __attribute__((always_inline)) {
-      float head[NSY], mid = 0.0f, tail = 0.0f;
-      head[2 * R] = 0.0f;
+  // ---- per cell and shift row: S, or Q, the sums of B' - Kc (and of its
+  // square) along the row of column sums; the columns of the cells beside it
+  // are brought to Kc first
+  constexpr int kItems = C::NC * NSY, kArr = kItems * NSY;
+  constexpr float n = (float)STEP, kInvN = 1.0f / (float)(C::WIN * C::WIN);
+  float SQ[NSY];
+  if (t < 2 * kItems) {
+    const bool sq = t >= kItems;
+    const int it = sq ? t - kItems : t, c = it / NSY, k = it - c * NSY, ci = c / C::CW, cj = c - ci * C::CW;
+    const float* vs = sV + (ci * NSY + k) * C::BP + cj * STEP;
+    const float Kc = s_cell[0][c];
+    const float dl = s_cell[0][cell_of(ci, cj * STEP)] - Kc, dr = s_cell[0][cell_of(ci, cj * STEP + C::BRW - 1)] - Kc;
+    float col[C::BRW];
+    if (sq) {
 #pragma unroll
-      for (int x = 2 * R - 1; x >= 0; --x) head[x] = head[x + 1] + p[x];
-#pragma unroll
-      for (int x = 2 * R; x < C::WIN; ++x) mid += p[x];
-#pragma unroll
-      for (int j = 0; j < NSY; ++j) {
-        if (j > 0) tail += p[C::WIN + j - 1];
-        o[j] = head[j] + mid + tail;
+      for (int x = 0; x < C::BRW; ++x) {
+        const float d = x < R ? dl : dr;
+        col[x] = vs[C::VS + x];
+        if (x < R || x >= R + STEP) col[x] += d * (2.0f * vs[x] + n * d);
       }
-    };
-    const float* vs = sV + (wi * NSY + k) * C::BP + wj * STEP;
-    boxes(vs, S);
-    boxes(vs + C::VS, Q);
-    const float* p00 = sB + (k * C::NC + c00) * C::PP;
-    const float* p10 = p00 + C::CW * C::PP;
-    float best = -2.0f;
-    int bkey = 1 << 20;
-    bool allflat = true;
+    } else {
+#pragma unroll
+      for (int x = 0; x < C::BRW; ++x) {
+        col[x] = vs[x];
+        if (x < R || x >= R + STEP) col[x] += n * (x < R ? dl : dr);
+      }
+    }
+    float head[NSY], mid = 0.0f, tail = 0.0f;
+    head[2 * R] = 0.0f;
+#pragma unroll
+    for (int x = 2 * R - 1; x >= 0; --x) head[x] = head[x + 1] + col[x];
+#pragma unroll
+    for (int x = 2 * R; x < STEP; ++x) mid += col[x];
 #pragma unroll
     for (int j = 0; j < NSY; ++j) {
-      const int sx = j - R;
-      const float Pw = (p00[j] + p00[C::PP + j]) + (p10[j] + p10[C::PP + j]);
-      const float num = Pw - meanA * S[j];
-      const float varB = Q[j] - S[j] * S[j] * kInvN;
-      const bool flat = flatA || !(varB > kFlatRel * Q[j]);
-      const float r = flat ? 0.0f : num * __builtin_amdgcn_rsqf(varA * varB);
-      s_rho[t * NSY + j] = r;
-      const bool used = !g.fixed || sx == 0 || sy == 0;
-      if (used) {
-        allflat = allflat && flat;
-        const int key = tie_key(sy, sx);
-        if (better(r, key, best, bkey)) {
-          best = r;
-          bkey = key;
-        }
-      }
+      if (j > 0) tail += col[STEP + j - 1];
+      SQ[j] = head[j] + mid + tail;
     }
-    s_best[t] = best;
-    s_key[t] = (bkey << 1) | (allflat ? 1 : 0);
+  }
+  // per window: its mean Kw, per cell d = Kc - Kw, and the sums of A - Kw and
+  // its square
+  auto cell_at = [](int w, int i) { return (w / TW + (i >> 1)) * C::CW + w - (w / TW) * TW + (i & 1); };
+  if (t >= NT - C::NWIN) {
+    const int w = NT - 1 - t;
+    float Kw = 0.0f, s1 = 0.0f, sa = 0.0f, saa = 0.0f, cp = 0.0f, cs = 0.0f, cq = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      Kw += 0.25f * s_cell[0][cell_at(w, i)];
+      s1 += s_cell[1][cell_at(w, i)];
+    }
+    Kw = rintf(Kw + s1 * kInvN);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int c = cell_at(w, i);
+      const float d = s_cell[0][c] - Kw, e = n * n * d, f = s_cell[1][c] + e;
+      s_win[w][i] = d;
+      sa += f;
+      saa += s_cell[2][c] + d * (s_cell[1][c] + f);
+      cp += d * f;
+      cs += e;
+      cq += d * e;
+    }
+    const float mA = sa * kInvN, varA = saa - sa * mA;
+    s_win[w][4] = mA;
+    s_win[w][5] = varA > kFlatRel * saa ? varA : 0.0f;   // (0: flat)
+    s_win[w][6] = cp;
+    s_win[w][7] = cs;
+    s_win[w][8] = cq;
+    s_sharp[w] = 0;
+  }
+  __syncthreads();   // tiles and column sums are read: the cells' sums take their place
+  if (t < C::NI && part == 0) {
+#pragma unroll
+    for (int j = 0; j < NSY; ++j) s_mem[q * NSY + j] = P[j];
+  }
+  if (t < 2 * kItems) {
+#pragma unroll
+    for (int j = 0; j < NSY; ++j) s_mem[kArr + t * NSY + j] = SQ[j];
   }
   __syncthreads();
-  // ---- a thread per window: its peak, fit, composition
-  if (t < C::NWIN) {
-    const int wi = t / TW, a = a0 + wi, b = b0 + t - wi * TW;
-    if (a < g.ny && b < g.nx) {
-      float best = -2.0f;
-      int bkey = 1 << 20;
-      bool allflat = true;
+  // ---- a thread per window, shift row and JG shift columns: the coefficients
+  constexpr int NS = NSY * NSY, JG = C::JG, NJ = (NSY + JG - 1) / JG;
+  if (t < C::NWIN * NSY * NJ) {
+    const int wk = t / NJ, j0 = (t - wk * NJ) * JG, w = wk / NSY, k = wk - w * NSY;
+    float v[12];
 #pragma unroll
-      for (int k = 0; k < NSY; ++k) {
-        const int kk = s_key[t * NSY + k];
-        const float r = s_best[t * NSY + k];
-        allflat = allflat && (kk & 1);
-        if (better(r, kk >> 1, best, bkey)) {
-          best = r;
-          bkey = kk >> 1;
-        }
+    for (int i = 0; i < 12; i += 4) *reinterpret_cast<float4*>(v + i) = *reinterpret_cast<const float4*>(&s_win[w][i]);
+    const float mA = v[4], varA = v[5];
+    const float* p = s_mem + cell_at(w, 0) * NS + k * NSY + j0;
+    bool sharp = false;
+#pragma unroll
+    for (int j = 0; j < JG; ++j) {
+      if (j0 + j >= NSY) break;
+      float Pw = v[6], Sw = v[7], Qw = v[8], ds = 0.0f;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const float* q = p + ((c >> 1) * C::CW + (c & 1)) * NS + j;
+        const float Sc = q[kArr];
+        Pw += q[0];
+        Sw += Sc;
+        Qw += q[2 * kArr];
+        ds += v[c] * Sc;
       }
-      int sy = 0, sx = 0;
-      if (!g.fixed) {
-        sx = (bkey & 63) - 32;
-        sy = ((bkey >> 6) & 63) - 32;
-      }
-      const float* rr = s_rho + t * NSY * NSY;
-      auto rhof = [&](int y, int x) { return rr[(y + R) * NSY + x + R]; };
-      auto node = [&](int c, int y, int x) { return s_node[c][y - nlo_y][x - nlo_x]; };
-      float pu = 0.0f, pv = 0.0f;
-      if (Pn) window_mean_half_overlap(a, b, g.nx, g.ny, node, pu, pv);
-      finish_vector(g, pair, a, b, sy, sx, allflat, pu, pv, rhof);
+      Pw += ds;
+      Qw += 2.0f * ds;
+      const float num = Pw - mA * Sw;
+      const float varB = Qw - Sw * Sw * kInvN;
+      const bool flat = varA == 0.0f || !(varB > kFlatRel * Qw);
+      s_rho[w * NS + k * NSY + j0 + j] = flat ? 0.0f : num * __builtin_amdgcn_rsqf(varA * varB);
+      sharp = sharp || (!flat && (!g.fixed || k == R || j0 + j == R));
     }
+    if (sharp) s_sharp[w] = 1;
+  }
+  __syncthreads();
+  // ---- GL lanes per window (a wave each, or 16 where a tile has more windows
+  // than waves): its peak; the first of them fits and composes
+  constexpr int GL = C::NWIN <= NT / 64 ? 64 : 16;
+  static_assert(C::NWIN * GL <= NT, "a group of lanes per window");
+  const int gl = t & (GL - 1), w = t / GL, wi = w / TW, a = a0 + wi, b = b0 + w - wi * TW;
+  float best = -2.0f;
+  int bkey = 1 << 20;
+  if (w < C::NWIN) {
+#pragma unroll
+    for (int i = 0; i < (NS + GL - 1) / GL; ++i) {
+      const int s = gl + GL * i, k = s / NSY, key = tie_key(k - R, s - k * NSY - R);
+      const float r = s_rho[w * NS + min(s, NS - 1)];
+      if (s < NS && better(r, key, best, bkey)) {
+        best = r;
+        bkey = key;
+      }
+    }
+  }
+  // (keys are below 2^20: exact as floats)
+  if constexpr (GL == 64) {
+    const float top = wave_max(best);
+    bkey = (int)wave_min(best == top ? (float)bkey : 1048576.0f);
+  } else {
+    auto rows = [](float x, auto op) __attribute__((always_inline)) {
+      auto dpp = [](float v, auto ctrl) {
+        const int i = __float_as_int(v);
+        return __int_as_float(__builtin_amdgcn_update_dpp(i, i, decltype(ctrl)::value, 0xF, 0xF, false));
+      };
+      x = op(x, dpp(x, Int<0xB1>()));
+      x = op(x, dpp(x, Int<0x4E>()));
+      x = op(x, dpp(x, Int<0x141>()));
+      return op(x, dpp(x, Int<0x140>()));
+    };
+    const float top = rows(best, [](float x, float y) { return fmaxf(x, y); });
+    bkey = (int)rows(best == top ? (float)bkey : 1048576.0f, [](float x, float y) { return fminf(x, y); });
+  }
+  if (gl == 0 && w < C::NWIN && a < g.ny && b < g.nx) {
+    int sy = 0, sx = 0;
+    if (!g.fixed) {
+      sx = (bkey & 63) - 32;
+      sy = ((bkey >> 6) & 63) - 32;
+    }
+    const float* rr = s_rho + w * NS;
+    auto rhof = [&](int y, int x) { return rr[(y + R) * NSY + x + R]; };
+    auto node = [&](int c, int y, int x) { return s_node[c][y - nlo_y][x - nlo_x]; };
+    float pu = 0.0f, pv = 0.0f;
+    if (Pn) window_mean_half_overlap(a, b, g.nx, g.ny, node, pu, pv);
+    finish_vector(g, pair, a, b, sy, sx, s_sharp[w] == 0, pu, pv, rhof);
   }
 }
 
