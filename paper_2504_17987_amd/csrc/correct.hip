@@ -1636,10 +1636,15 @@ void k_correct_bands(CorrArgs g) {
 // with six a SIMD would hold two waves of a workgroup or one, and a launch
 // of 384 threads runs 15% (24 px) and 4% (central) longer.  What bounds it
 // now is VALU issue (24 px: 450 of 524 us; central 131 of 175 us), beside it
-// latency.  Every sum runs in the band kernel's order.  8 x 4K u16, 24 px
-// windows: 606 -> 524 us (three waves with the A cell in 72 of 256
-// registers, 9 spilled); 16 x 1000 x 760 u8 central: 215 -> 175 us
-// (k_correct_tiled).
+// latency.  24 px windows: A as it is against B' - K, every sum in the band
+// kernel's order; 8 x 4K u16 606 -> 524 us (three waves with the A cell in
+// 72 of 256 registers, 9 spilled).  kCentral: A' is brought to K in LDS once
+// the tile's sum is known, so that (A' - K)(B' - K) is summed as in
+// k_correct_tiled, which served these windows (with A' as it is, bright
+// frames were up to 3e-3 off in the coefficient, now 5e-6; 3,400 of 12 bits,
+// particles of 150), and K is the mean of the tile's pixels inside the image,
+// so that tiles over its edge lose no bits either (k_correct_tiled 2e-3);
+// 16 x 1000 x 760 u8 215 -> 178 us (k_correct_tiled).
 // ---------------------------------------------------------------------------
 template <int N>
 using Int = std::integral_constant<int, N>;
@@ -1958,15 +1963,16 @@ void k_correct_halves(CorrArgs g) {
       unpack(wd, an);
     }
   };
-  // K, the rounded mean of the A tile, and the cells' sums of A - K and its
-  // square (rows dealt to the bands, by the second wave of each)
+  // K, the rounded mean of the A tile (kCentral: A' is held about it, too),
+  // and the cells' sums of A - K and its square (rows dealt to the bands, by
+  // the second wave of each)
   float K;
   auto cell_sums = [&]() __attribute__((always_inline)) {
     float s1 = 0.0f, s2 = 0.0f;
     auto add = [&](const float (&an)[STEP]) __attribute__((always_inline)) {
 #pragma unroll
       for (int x = 0; x < STEP; ++x) {
-        const float d = an[x] - K;
+        const float d = kCentral ? an[x] : an[x] - K;
         s1 += d;
         s2 += d * d;
       }
@@ -2000,7 +2006,15 @@ void k_correct_halves(CorrArgs g) {
     K = 0.0f;
 #pragma unroll
     for (int i = 0; i < NT / 64; ++i) K += s_red[i];
-    K = rintf(K / (float)(C::AH * C::AW));
+    // (of the pixels inside the image: the last tiles reach beyond it)
+    const int nin = (min(y0 + C::AH, g.H) - max(y0, 0)) * (min(x0 + C::AW, g.W) - max(x0, 0));
+    K = rintf(K / (float)nin);
+    constexpr int AQ = C::AW / 4;
+    for (int i = t; i < C::AH * AQ; i += NT) {
+      float4* p = reinterpret_cast<float4*>(sA + (i / AQ) * C::AP) + (i - (i / AQ) * AQ);
+      const float4 v = *p;
+      *p = make_float4(v.x - K, v.y - K, v.z - K, v.w - K);
+    }
   } else {
     // (integers: the waves' sums meet exactly)
     int isum = 0;
@@ -2048,9 +2062,9 @@ void k_correct_halves(CorrArgs g) {
     const float h = x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130, 0xF, 0xF, false));
     return h + __int_as_float(__builtin_amdgcn_ds_bpermute((lane + C::CW) << 2, __float_as_int(h)));
   };
-  // P = sum A (B' - K) of the shift columns J0 .. J0 + NJ - 1: the B' rows of
-  // the band streamed once each; B' row rb meets A row rb - k for shift row
-  // k, so the last SYG A rows are kept
+  // P = sum A (B' - K) (kCentral: of (A' - K) (B' - K)) of the shift columns
+  // J0 .. J0 + NJ - 1: the B' rows of the band streamed once each; B' row rb
+  // meets A row rb - k for shift row k, so the last SYG A rows are kept
   auto products = [&](auto j0_c, auto nj_c, float (&P)[SYG][C::H1]) __attribute__((always_inline)) {
     constexpr int J0 = decltype(j0_c)::value, NJ = decltype(nj_c)::value, NB = STEP + NJ - 1;
 #pragma unroll
@@ -2169,7 +2183,7 @@ void k_correct_halves(CorrArgs g) {
     constexpr float kInvN = 1.0f / (float)(4 * STEP * STEP);
     const float mA = sa * kInvN;
     const float varA = saa - sa * mA;
-    const float meanA = K + mA;
+    const float meanA = kCentral ? mA : K + mA;   // (of what the products took)
     const bool flatA = !(varA > kFlatRel * saa);
     float rv[SYG][NJ];
     bool allflat = true;   // every used shift of the wave is flat

@@ -88,3 +88,22 @@ def test_nearly_constant_window_off_its_surroundings(W, H, dtype, level, up, war
         assert fo[a, b] == 0 and po[a, b] == pytest.approx(1.0)
         assert f[a, b] == 0 and abs(p[a, b] - 1.0) < OWN_MEAN and np.abs(d[:, a, b] - do[:, a, b]).max() < 0.01, (
             a, b, f[a, b], p[a, b], d[:, a, b])
+
+
+@pytest.mark.parametrize("W,H", [(264, 200), (520, 400)])
+@pytest.mark.parametrize("dtype,light", [("u8", (200, 10, 25)), ("u16", (3000, 100, 300))])
+def test_bright_frames_both_deformed_16px(W, H, dtype, light):
+    """16 px windows with both frames deformed: bright frames whose level
+    varies little over a tile of windows, on grids that end inside a tile.
+    (The sums run about the tile's mean, and the light's swing is at most
+    twice the particles' standard deviation: terms at most 4 or 5 times the
+    result's size, within the usual 2e-5.)"""
+    from paper_2504_17987_amd import api
+    say(f"[bright frames, 16 px, both deformed] {W}x{H} {dtype}")
+    (A, B), flow = _lit_pair(W, H, dtype == "u16", *light, 2.5)
+    pred = (np.round(2 * synth.truth(flow, W, H, 8)) / 2).astype(np.float32)
+    do, po, fo = oracle.correct(A, B, 16, 8, 4, pred.astype(np.float64), 1, 0)
+    P = api.Plan(W, H, win=16, step=8, radius=4, levels=1, radius_coarse=4, dtype=dtype, warp="central")
+    d, p, f = (x.cpu().numpy()[0] for x in P.correct(_dev(A), _dev(B), torch.from_numpy(pred[None]).cuda()))
+    compare_correct(None, None, A.astype(float), B.astype(float), 16, 8, 4, pred.astype(np.float64), d, p, f, do, po, fo,
+                    mode=1, where=f"bright frames [{W}x{H} {dtype}]")
