@@ -1925,7 +1925,7 @@ void k_correct_halves(CorrArgs g) {
         } else {
           v = pixf<T>(img, g.pitch, g.W, g.H, y, x);
         }
-        sum += v;
+        sum += v == v ? v : 0.0f;   // (a node that is not finite leaves the other windows' K alone)
         dst[r * DP + q] = v - K;
       }
     }
@@ -2543,7 +2543,8 @@ __global__ __launch_bounds__(NT) void k_correct_rows(CorrArgs g) {
           out[e] = v - K;
         }
       }
-      sum += (out[0] + out[1]) + (out[2] + out[3]);
+      const float s4 = (out[0] + out[1]) + (out[2] + out[3]);
+      sum += s4 == s4 ? s4 : 0.0f;   // (a node that is not finite leaves the other windows' K alone)
       *reinterpret_cast<float4*>(dst + r * pitch + q) = make_float4(out[0], out[1], out[2], out[3]);
     }
     return sum;
