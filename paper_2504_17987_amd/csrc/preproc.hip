@@ -352,64 +352,49 @@ __global__ __launch_bounds__(NT) void k_clahe_lut(const uint8_t* __restrict__ in
   __syncthreads();
   uint32_t* hc = hist + (lane & (NH - 1));
   const uint8_t* src = in + (int64_t)pair * stride;
-  const int rowbytes = W * ES;
-  const int w0 = (xa * ES) >> 2, nw = ((xb * ES + 3) >> 2) - w0;   // the tile's words of a row
   auto count = [&](uint32_t v) __attribute__((always_inline)) {
     if (v) atomicAdd(&hc[(v >> SH) * NH], 1u);
   };
-  // Items of four words: nc per row, dealt to the threads in order, U of a
-  // thread's items requested together.  An item whose words all lie in the
-  // tile takes one 16-byte read; those at its sides go word by word and
-  // pixel by pixel.
-  const int nc = (nw + 3) >> 2, items = nc * th;
+  // Items of four words that lie in the tile: nc per row, dealt to the
+  // threads in order, U of a thread's items requested together.
+  const int wa = (xa * ES + 3) >> 2, nc = max(((xb * ES) >> 2) - wa, 0) >> 2, items = nc * th;
   constexpr int U = 4;
   struct __attribute__((aligned(4))) Four { uint32_t w[4]; };
-  const int srow = NT / nc, scol = NT - srow * nc;   // one step of NT items
-  int ry = t / nc, rc = t - ry * nc;                 // the thread's next item
+  const int srow = NT / max(nc, 1), scol = NT - srow * nc;   // one step of NT items
+  int ry = t / max(nc, 1), rc = t - ry * nc;                 // the thread's next item
   for (int p0 = t; p0 < items; p0 += U * NT) {
     Four v[U];
-    int c[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      c[u] = 4 * rc;
-      const uint8_t* row = src + (int64_t)(ya + min(ry, th - 1)) * pitch;
-      const int xw = 4 * (w0 + c[u]);
+      v[u] = *reinterpret_cast<const Four*>(src + (int64_t)(ya + min(ry, th - 1)) * pitch + 4 * (wa + 4 * rc));
       ry += srow;
       rc += scol;
       if (rc >= nc) {
         rc -= nc;
         ++ry;
       }
-      if (xw + 16 <= rowbytes) {
-        v[u] = *reinterpret_cast<const Four*>(row + xw);
-      } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[u].w[k] = masked_word(row, rowbytes, xw + 4 * k);
-      }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (p0 + u * NT >= items) break;
-      const int x = PW * (w0 + c[u]);   // first pixel of the item
-      if (x >= xa && x + 4 * PW <= xb) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+      for (int k = 0; k < 4; ++k)
 #pragma unroll
-          for (int e = 0; e < PW; ++e) count(ES == 1 ? (v[u].w[k] >> (8 * e)) & 0xffu : (v[u].w[k] >> (16 * e)) & 0xffffu);
-      } else {
-#pragma unroll 1
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t wd = v[u].w[0];
-          v[u].w[0] = v[u].w[1];
-          v[u].w[1] = v[u].w[2];
-          v[u].w[2] = v[u].w[3];
+        for (int e = 0; e < PW; ++e) count(ES == 1 ? (v[u].w[k] >> (8 * e)) & 0xffu : (v[u].w[k] >> (16 * e)) & 0xffffu);
+    }
+  }
+  // The words left at the sides of a row, the first and last of them partly
+  // the tile's, word by word and pixel by pixel (as lanes of the loop above
+  // they cost every wave their steps: 16 u8 frames of 1000 x 760, a tile
+  // each, 351 us both passes, now 103)
+  const int w0 = (xa * ES) >> 2, nl = wa - w0, ns = nl + ((xb * ES + 3) >> 2) - (wa + 4 * nc);
+  for (int p = t; p < th * ns; p += NT) {
+    const int r = p / ns, k = p - r * ns, w = k < nl ? w0 + k : wa + 4 * nc + k - nl;
+    const uint32_t wd = masked_word(src + (int64_t)(ya + r) * pitch, W * ES, 4 * w);
 #pragma unroll
-          for (int e = 0; e < PW; ++e) {
-            const int px = x + k * PW + e;
-            if (px >= xa && px < xb) count(ES == 1 ? (wd >> (8 * e)) & 0xffu : (wd >> (16 * e)) & 0xffffu);
-          }
-        }
-      }
+    for (int e = 0; e < PW; ++e) {
+      const int px = PW * w + e;
+      if (px >= xa && px < xb) count(ES == 1 ? (wd >> (8 * e)) & 0xffu : (wd >> (16 * e)) & 0xffffu);
     }
   }
   __syncthreads();

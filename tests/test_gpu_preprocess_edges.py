@@ -46,3 +46,16 @@ def test_clahe_cells(dtype, bits, W, H, pad, tiles):
     assert np.array_equal(host(Id).astype(np.int64), ref.astype(np.int64))
     if pad:
         assert (host(full)[:, :, W:] == np.iinfo(I.dtype).max).all()
+
+
+# histograms of tiles that begin and end anywhere in a word, narrower than a
+# word, than the four words of a read, and with one to five words at the sides
+@pytest.mark.parametrize("dtype,bits", [("u8", 8), ("u16", 12)])
+@pytest.mark.parametrize("W,tiles_x", [(46, 46), (46, 13), (46, 2), (130, 7), (150, 4), (198, 7), (198, 1), (202, 3)])
+def test_clahe_tile_sides(dtype, bits, W, tiles_x):
+    I = np.random.default_rng(W + tiles_x).integers(0, 1 << bits, (2, 22, W)).astype(np.uint8 if dtype == "u8" else np.uint16)
+    I[:, ::2, ::3] = 0
+    Id = dev(I, dtype, 2)
+    out = host(plan_for(W, 22, 2, dtype, bits).clahe(Id, out_like(Id, 2), tiles=(tiles_x, 2), clip_factor=3.0))
+    ref = np.stack([oracle.clahe(I[i], bits, tiles_x, 2, 3.0) for i in range(2)])
+    assert np.array_equal(out.astype(np.int64), ref.astype(np.int64))
