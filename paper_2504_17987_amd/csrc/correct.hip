@@ -2279,9 +2279,9 @@ void k_correct_halves(CorrArgs g) {
 // with particles of 300 under light of 3000 +- 600, error of the coefficient
 // 0.8e-6 at most, as about each window's mean by itself; about the mean of a
 // tile of windows, and with A as it is, 42e-6.  4 x 1024 x 512 u8 frames, r 4:
-// 37.5 us, 22.6 of VALU issue and 20 of LDS reads side by side (34.3 us about
-// the tile's mean; k_correct_generic 454); one 256 x 256 pair, r 8: 14.2 us
-// (generic 36).
+// 36.8 us, 22.6 of VALU issue beside 16.6 of LDS accesses (33.5 us about the
+// tile's mean; k_correct_generic 454); one 256 x 256 pair, r 8: 13.8 us
+// (generic 36), the latency of seven phases.
 // Frames are deformed by the whole predictor (B only), or by half of it each
 // (kCentral; A' is then held as floats, else the packed pixels are).
 // ---------------------------------------------------------------------------
@@ -2902,6 +2902,9 @@ hipError_t launch_tiled_t(const CorrArgs& g, int n, hipStream_t s) {
     if (!g.central && g.step == 12 && g.R == 4) return launch_halves<T, 12, false>(g, n, s);
   }
   if (g.step == 8 && g.R == 4) return launch_halves<T, 8, true>(g, n, s);
+  // The others stay with the tiled kernel: with both 24 px frames deformed,
+  // A' as floats would take two waves per band to 118 KB of LDS, one
+  // workgroup a CU; the nine shifts of r 1 make no bands to share.
   if (g.step == 8 && g.R == 1) return launch_tiled<T, 8, 1, 1, 8, 8, 256>(g, n, s);
   if (g.step == 12 && g.R == 4) return launch_tiled<T, 12, 4, 3, 5, 5, 128>(g, n, s);
   if (g.step == 12 && g.R == 1) return launch_tiled<T, 12, 1, 1, 5, 5, 128>(g, n, s);

@@ -31,9 +31,13 @@ namespace {
 // pixel count of the clipped box is a product of two clipped spans; the
 // quotient comes from a float reciprocal, corrected to the exact floor.
 // ---------------------------------------------------------------------------
-// Rows of a band: more bands hide latency, each adds 2r rows to read.  r 7,
-// 64 x 1 MP u8: 54 us with 32, 62 with 64, 79 with 128; r 5, 8 x 4K u16: 73,
-// 68 and 86 us.
+// Rows of a band: more bands hide latency, each adds 2r rows to read.  Full
+// chips, calls of 64 x 1 MP u8 with 16, 32 and 64 rows: r 3 43.5, 44.1 and
+// 45.0 us, r 7 49.8, 48.9 and 49.6, r 12 65.5, 63.6 and 58.5, r 16 78.8, 75.1
+// and 81.5; 8 x 4K u16 with 32, 64 and 128: r 3 57.0, 58.2 and 72.5, r 5
+// 62.1, 61.5 and 70.1, r 12 81.9, 82.1 and 83.3, r 16 100.3, 99.7 and 118.5.
+// (One frame alone would gain from shorter bands: one of 4K u16, r 5, 28 us
+// with 64 rows and 14 with 16.)
 template <typename T>
 constexpr int hp_band() { return sizeof(T) == 1 ? 32 : 64; }
 
@@ -308,9 +312,9 @@ __global__ __launch_bounds__(64) void k_highpass(const uint8_t* __restrict__ in,
 // image's background) are what the other bins leave of the tile's pixels.
 // Reads take 16 bytes a lane, several in flight.  What a tile costs is the
 // instructions per pixel (about 4 and an LDS atomic), so u16 tiles, few and
-// large, get 1,024 threads: 8 frames of 4K u16 on 7 x 5 tiles 224 -> 72 us
+// large, get 1,024 threads: 8 frames of 4K u16 on 7 x 5 tiles 224 -> 43 us
 // (one word per thread and step, a division each, 256 threads; the number of
-// copies, 1 to 4, changes nothing), 64 x 1 MP u8 on 8 x 8 tiles 44 -> 22 us.
+// copies, 1 to 4, changes nothing), 64 x 1 MP u8 on 8 x 8 tiles 44 -> 21 us.
 // Then the clip at max(1, floor(clip * npix / nbins)) (the same double
 // arithmetic as the host), the clipped excess spread evenly
 // (excess / nbins to every bin, one more to the first `rest` bins at a
