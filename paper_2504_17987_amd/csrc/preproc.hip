@@ -60,7 +60,9 @@ __device__ __forceinline__ uint32_t udiv_small(uint32_t s, uint32_t c) {
 // (so that M < 2^32), keeps its error s (M D - 2^(32+k)) / D below
 // 2^(32+k) / D > 2^31 > s, hence exact.  u8 (s < 2^19): the same with a
 // 32-bit product of 24-bit factors at full rate, floor(s M / 2^K) with
-// M = ceil(2^K / D), exact while s (M D - 2^K) < 2^K and s M < 2^32.
+// M = ceil(2^K / D), exact while s (M D - 2^K) < 2^K and s M < 2^32 (tested
+// here at compile time; radii 9, 10 and 12 to 16 have no such K and take the
+// u16 product).
 template <int D, bool kByte>
 struct BoxDiv {
   static constexpr int K = []() { int k = 0; while ((1 << (k + 1)) < D) ++k; return k; }();
